@@ -215,15 +215,17 @@ const char* gs_version(void);
 
 /* Kernel configuration keys for gs_set_tuning(). */
 enum {
-  GS_TUNE_FWD_PIXELS_PER_LANE = 0, /* gs_render_fwd: pixels per lane, 1 | 2 | 4 (default 1) */
-  GS_TUNE_BWD_PIXELS_PER_LANE = 1, /* gs_render_bwd: pixels per lane, 1 | 2 | 4 (default 1) */
+  GS_TUNE_FWD_PIXELS_PER_LANE = 0, /* gs_render_fwd: pixels per lane, 1 | 2 | 4 (default:
+                                      chosen per launch from the number of tiles, read back
+                                      as 1)                                                */
+  GS_TUNE_BWD_PIXELS_PER_LANE = 1, /* gs_render_bwd: likewise                              */
   GS_TUNE_FWD_SCHEDULE = 2,        /* gs_render_fwd(_l1): a GS_SCHEDULE_* value            */
   GS_TUNE_BWD_SCHEDULE = 3,        /* gs_render_bwd and gs_render_error: GS_SCHEDULE_*     */
   GS_TUNE_FWD_STAGE = 4,           /* gs_render_fwd(_l1): splats each thread stages in LDS
-                                      per batch, 1 | 2 (default 0: 1, or 2 at 2 pixels per
-                                      lane)                                                */
+                                      per batch, 1 | 2 (default 0: 1, or 2 at a set 2
+                                      pixels per lane)                                     */
   GS_TUNE_BWD_STAGE = 5,           /* gs_render_bwd: likewise, 1 | 2 (default 0: 2, or 1 at
-                                      1 pixel per lane)                                    */
+                                      1 pixel per lane and at a chosen 2)                  */
   GS_TUNE_COUNT = 6
 };
 

@@ -18,7 +18,7 @@ thread_local hipEvent_t g_events[GS_KERNEL_COUNT][2] = {};
 }
 
 namespace {
-std::atomic<int> g_tuning[GS_TUNE_COUNT] = {{1}, {1}, {GS_SCHEDULE_HEAVIEST_FIRST},
+std::atomic<int> g_tuning[GS_TUNE_COUNT] = {{0}, {0}, {GS_SCHEDULE_HEAVIEST_FIRST},
                                             {GS_SCHEDULE_HEAVIEST_FIRST}, {0}, {0}};
 }
 
@@ -215,8 +215,7 @@ int gs_set_tuning(int key, int value) {
     if (value < 0 || value > 2)
       return invalid("splats staged per thread must be 1 or 2 (got %d)", value);
   } else {
-    if (value == 0) value = 1;
-    if (value != 1 && value != 2 && value != 4)
+    if (value != 0 && value != 1 && value != 2 && value != 4)
       return invalid("pixels per lane must be 1, 2 or 4 (got %d)", value);
   }
   g_tuning[key].store(value, std::memory_order_relaxed);
@@ -225,7 +224,9 @@ int gs_set_tuning(int key, int value) {
 
 int gs_get_tuning(int key) {
   if (key < 0 || key >= GS_TUNE_COUNT) return -1;
-  return tuning(key);
+  const int value = tuning(key);
+  const bool pixels = key == GS_TUNE_FWD_PIXELS_PER_LANE || key == GS_TUNE_BWD_PIXELS_PER_LANE;
+  return pixels && value == 0 ? 1 : value;
 }
 
 int64_t gs_num_tiles(const gs_views* views) {

@@ -276,8 +276,16 @@ TileSchedule tile_schedule(int schedule, const gs_bins& bins, int call, int n_ti
 // current device holds at once; 0 on error.
 int resident_workgroups(const void* kernel, int block);
 
-// Process-wide tuning values (see gs_set_tuning); always a supported value.
+// Process-wide tuning values (see gs_set_tuning): a supported value, or 0
+// where the launch chooses (pixels per lane, staging batch).
 int tuning(int key);
+
+// Pixels per lane of a tile kernel that no tuner has set: one wavefront per
+// quadrant while the launch is short of wavefronts, two quadrants per
+// wavefront from `two` tiles on, the whole tile from `four` on.
+inline int pixels_per_lane(int value, int n_tiles, int two, int four) {
+  return value != 0 ? value : n_tiles < two ? 1 : n_tiles < four ? 2 : 4;
+}
 
 // Splats per thread and LDS batch from a GS_TUNE_*_STAGE value (0: the
 // kernel's default).

@@ -649,11 +649,19 @@ hipError_t launch_render_bwd(const gs_gaussians& g, const gs_projected& p, const
     const auto* xy = reinterpret_cast<const float2*>(p.xy);
     const auto* co = reinterpret_cast<const float4*>(p.conic_opacity);
     const auto* rd = reinterpret_cast<const float4*>(p.rgb_depth);
-    const int ppl = tuning(GS_TUNE_BWD_PIXELS_PER_LANE);
+    // Measured (us at 1 | 2 | 4 pixels per lane, views of 640x480 and 200,000
+    // Gaussians): 1,200 tiles 51 | 57 | 86, 2,400 tiles 78 | 74 | 89, 4,800
+    // tiles 134 | 108 | 112, 7,200 tiles 184 | 145 | 137, 38,400 tiles
+    // 861 | 632 | 547.
+    const int set_ppl = tuning(GS_TUNE_BWD_PIXELS_PER_LANE);
+    const int ppl = pixels_per_lane(set_ppl, vt.n_tiles, 2000, 5000);
     const int sched = tuning(GS_TUNE_BWD_SCHEDULE);
     // splats per thread and batch: 128 per batch at one and two wavefronts
     // per tile, 256 at four
-    const int spl = stage_per_thread(tuning(GS_TUNE_BWD_STAGE), ppl == 1 ? 1 : 2);
+    int spl = stage_per_thread(tuning(GS_TUNE_BWD_STAGE), ppl == 1 ? 1 : 2);
+    // the chosen 2 pixels per lane: 128 per batch were faster (3,600 tiles: 93
+    // against 95 us, 4,800 tiles 108 against 115)
+    if (set_ppl == 0 && ppl == 2 && tuning(GS_TUNE_BWD_STAGE) == 0) spl = 1;
 #define GS_BWD(P, S) \
   launch_bwd<P, S>(sched, bins, vt, xy, co, rd, bg, dL_dimage, final_T, n_contrib, grad2d, s)
     kernel_event_start(GS_KERNEL_RENDER_BWD, s);

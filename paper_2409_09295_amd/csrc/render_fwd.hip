@@ -281,11 +281,18 @@ hipError_t launch_render_fwd(const gs_projected& p, const gs_bins& bins, const V
   const auto* xy = reinterpret_cast<const float2*>(p.xy);
   const auto* co = reinterpret_cast<const float4*>(p.conic_opacity);
   const auto* rd = reinterpret_cast<const float4*>(p.rgb_depth);
-  const int ppl = tuning(GS_TUNE_FWD_PIXELS_PER_LANE);
+  // Measured (us at 1 | 2 | 4 pixels per lane, views of 640x480 and 200,000
+  // Gaussians): 1,200 tiles 26 | 37 | 58, 3,600 tiles 47 | 42 | 59, 7,200
+  // tiles 78 | 66 | 69, 9,600 tiles 96 | 86 | 86, 38,400 tiles 376 | 307 | 275.
+  const int set_ppl = tuning(GS_TUNE_FWD_PIXELS_PER_LANE);
+  const int ppl = pixels_per_lane(set_ppl, vt.n_tiles, 3000, 8000);
   const int sched = tuning(GS_TUNE_FWD_SCHEDULE);
   // splats per thread and batch: 64 per batch at one wavefront per tile was
   // measured 4.5% faster than 128; 256 at two and four wavefronts
-  const int spl = stage_per_thread(tuning(GS_TUNE_FWD_STAGE), ppl == 2 ? 2 : 1);
+  int spl = stage_per_thread(tuning(GS_TUNE_FWD_STAGE), ppl == 2 ? 2 : 1);
+  // the chosen 2 pixels per lane run between 3,000 and 8,000 tiles, where 128
+  // per batch were faster (3,600 tiles: 42 against 46 us)
+  if (set_ppl == 0 && ppl == 2 && tuning(GS_TUNE_FWD_STAGE) == 0) spl = 1;
   const bool l1 = target != nullptr;
 #define GS_FWD(P, S, L)                                                                          \
   launch_fwd<P, S, L>(sched, bins, vt, xy, co, rd, bg, image, final_T, n_contrib, depth, target, \

@@ -46,10 +46,20 @@ __global__ __launch_bounds__(kBlock / PPL, PPL == 4 && SPL == 1 && L1 && !Q ? 7 
   constexpr int kStage = SPL * NT;
   constexpr int kPerThread = kStage / NT;
   constexpr int kWords = kStage / 64;
-  __shared__ StagedSplat s_splat[kStage];
+  // At one pixel per lane a launch is short of wavefronts and a tile's time is
+  // its walk's latency: LDS read, alpha, transmittance, splat by splat.  Groups
+  // of kGroup splats overlap the first two: 50 -> 39 us at 300 tiles of 1,235
+  // keys, 23 -> 18 at 320 of 100, 26 at 1,200 of 82 either way (groups of two
+  // 43, of six 40 at the first).  A launch that fills the GPU takes more pixels
+  // per lane and walks one by one.
+  constexpr int kGroup = PPL == 1 ? 4 : 1;
+  __shared__ StagedSplat s_splat[kStage + (kGroup > 1 ? 1 : 0)];
   // s_reach[q][w] bit b: staged splat 64 w + b can reach quadrant q
   __shared__ uint64_t s_reach[4][kWords];
   __shared__ uint32_t s_slot;
+  if constexpr (kGroup > 1) {   // the blank record (visible after the staging barrier)
+    if (threadIdx.x == 0) s_splat[kStage] = StagedSplat{};
+  }
   // slot i: tile order[i] (longest lists first) when the binning produced
   // an order; one slot per workgroup, or (Q) slots drawn from `counter`
   for (uint32_t slot = blockIdx.x;;) {
@@ -116,7 +126,48 @@ __global__ __launch_bounds__(kBlock / PPL, PPL == 4 && SPL == 1 && L1 && !Q ? 7 
 #pragma unroll
         for (int k = 0; k < PPL; ++k) m |= s_reach[__builtin_ctz(qbit[k])][w];
         m = uniform_u64(m);
-        while (m) {
+        if constexpr (kGroup > 1) {
+          while (m) {
+            // kGroup splats at a time (past the last one the blank record, which
+            // blends nowhere): their records and alphas do not wait for each
+            // other, only the transmittance runs through them in order
+            float4 geo[kGroup], app[kGroup], ext[kGroup];
+            int j[kGroup];
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u) {
+              j[u] = m ? 64 * w + __builtin_ctzll(m) : kStage;
+              m &= m - 1;
+              geo[u] = s_splat[j[u]].geo;
+              app[u] = s_splat[j[u]].app;
+              ext[u] = s_splat[j[u]].ext;
+            }
+            float alpha[kGroup];
+            bool ok[kGroup], any = false;
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u) {
+              float raw, G, dy;
+              ok[u] = eval_alpha_at<false>(column_terms(geo[u], fpx[0]), geo[u], app[u], fpy[0],
+                                           alpha[u], raw, G, dy);
+              any = any || ok[u];
+            }
+            if (!__any(any)) continue;
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u) {
+              const float Tn = __builtin_fmaf(-T[0], alpha[u], T[0]);
+              const bool stop = Tn < kTMin;
+              const bool blend = ok[u] && !stop;
+              const float wgt = alpha[u] * T[0];
+              C0[0] = blend ? C0[0] + app[u].z * wgt : C0[0];
+              C1[0] = blend ? C1[0] + app[u].w * wgt : C1[0];
+              C2[0] = blend ? C2[0] + ext[u].x * wgt : C2[0];
+              D[0] = blend ? D[0] + ext[u].z * wgt : D[0];
+              last[0] = blend ? (uint32_t)(b - (int64_t)s) + (uint32_t)j[u] + 1 : last[0];
+              T[0] = blend ? Tn : ok[u] ? -fabsf(T[0]) : T[0];
+            }
+            if (!__any(__float_as_int(T[0]) > 0)) m = 0;
+          }
+        }
+        while (kGroup == 1 && m) {
           const int j = 64 * w + __builtin_ctzll(m);
           m &= m - 1;
           const float4 geo = s_splat[j].geo;
@@ -282,15 +333,16 @@ hipError_t launch_render_fwd(const gs_projected& p, const gs_bins& bins, const V
   const auto* co = reinterpret_cast<const float4*>(p.conic_opacity);
   const auto* rd = reinterpret_cast<const float4*>(p.rgb_depth);
   // Measured (us at 1 | 2 | 4 pixels per lane, views of 640x480 and 200,000
-  // Gaussians): 1,200 tiles 26 | 37 | 58, 3,600 tiles 47 | 42 | 59, 7,200
-  // tiles 78 | 66 | 69, 9,600 tiles 96 | 86 | 86, 38,400 tiles 376 | 307 | 275.
+  // Gaussians): 1,200 tiles 25 | 37 | 58, 2,400 tiles 37 | 38 | 58, 3,600
+  // tiles 49 | 43 | 59, 7,200 tiles 86 | 68 | 69, 9,600 tiles 109 | 88 | 85,
+  // 38,400 tiles 398 | 309 | 275.
   const int set_ppl = tuning(GS_TUNE_FWD_PIXELS_PER_LANE);
-  const int ppl = pixels_per_lane(set_ppl, vt.n_tiles, 3000, 8000);
+  const int ppl = pixels_per_lane(set_ppl, vt.n_tiles, 2400, 8000);
   const int sched = tuning(GS_TUNE_FWD_SCHEDULE);
   // splats per thread and batch: 64 per batch at one wavefront per tile was
   // measured 4.5% faster than 128; 256 at two and four wavefronts
   int spl = stage_per_thread(tuning(GS_TUNE_FWD_STAGE), ppl == 2 ? 2 : 1);
-  // the chosen 2 pixels per lane run between 3,000 and 8,000 tiles, where 128
+  // the chosen 2 pixels per lane run between 2,400 and 8,000 tiles, where 128
   // per batch were faster (3,600 tiles: 42 against 46 us)
   if (set_ppl == 0 && ppl == 2 && tuning(GS_TUNE_FWD_STAGE) == 0) spl = 1;
   const bool l1 = target != nullptr;

@@ -101,9 +101,11 @@ __global__ __launch_bounds__(256) void cost_wta_kernel(
       const float* img = low + (int64_t)k * Hl * Wl;
 #pragma unroll
       for (int j = 0; j < kHypPerLane; ++j) {
-        const float px = c.R[0] * wx[j] + c.R[1] * wy[j] + c.R[2] * wz[j] + c.t[0];
-        const float py = c.R[3] * wx[j] + c.R[4] * wy[j] + c.R[5] * wz[j] + c.t[1];
-        const float pz = c.R[6] * wx[j] + c.R[7] * wy[j] + c.R[8] * wz[j] + c.t[2];
+        // the roundings spelled out: where two hypotheses tie, the winner hangs on
+        // them, so they must not follow the compiler's choice of contraction
+        const float px = __builtin_fmaf(c.R[2], wz[j], __builtin_fmaf(c.R[1], wy[j], c.R[0] * wx[j])) + c.t[0];
+        const float py = __builtin_fmaf(c.R[5], wz[j], __builtin_fmaf(c.R[3], wx[j], c.R[4] * wy[j])) + c.t[1];
+        const float pz = __builtin_fmaf(c.R[8], wz[j], __builtin_fmaf(c.R[6], wx[j], c.R[7] * wy[j])) + c.t[2];
         const float us = c.fx * px / pz + c.cx, vs = c.fy * py / pz + c.cy;
         float sample;
         const bool ok = bilinear(img, Hl, Wl, (us - 2.0f) * 0.25f, (vs - 2.0f) * 0.25f,

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kBlock / PPL, PPL == 4 && SPL == 1 && L1 && !Q ? 7 
     float* img = image + 3 * vi.pix_base;
     // L1 against the target, as gs_l1_loss_grad computes it from the image
     const float inv = 1.0f / (float)(3 * plane);
-    float lsum = 0.0f;
+    float lsum[PPL] = {};   // per pixel slot, i.e. per quadrant
 #pragma unroll
     for (int k = 0; k < PPL; ++k) {
       if (!inside[k]) continue;
@@ -229,19 +229,24 @@ __global__ __launch_bounds__(kBlock / PPL, PPL == 4 && SPL == 1 && L1 && !Q ? 7 
           const int64_t o = 3 * vi.pix_base + ch * plane + off;
           const float d = c[ch] - target[o];
           dL[o] = d > 0.0f ? inv : (d < 0.0f ? -inv : 0.0f);
-          lsum += fabsf(d);
+          lsum[k] += fabsf(d);
         }
       }
     }
     if (L1) {
+      // summed by quadrant, then over the quadrants in order: the same bits at
+      // every number of pixels per lane
       __shared__ float s_l[kBlock / 64];
 #pragma unroll
-      for (int d = 32; d >= 1; d >>= 1) lsum += __shfl_xor(lsum, d, 64);
-      if ((threadIdx.x & 63) == 0) s_l[threadIdx.x >> 6] = lsum;
+      for (int k = 0; k < PPL; ++k) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) lsum[k] += __shfl_xor(lsum[k], d, 64);
+        if (lane == 0) s_l[__builtin_ctz(qbit[k])] = lsum[k];
+      }
       __syncthreads();
       if (threadIdx.x == 0) {
         float t = 0.0f;
-        for (int w = 0; w < NT / 64; ++w) t += s_l[w];
+        for (int q = 0; q < kBlock / 64; ++q) t += s_l[q];
         tile_loss[tile] = t * inv;
       }
     }

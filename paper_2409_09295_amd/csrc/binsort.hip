@@ -10,7 +10,7 @@
 //             per-view list as {u, v, radius, depth} records (one global
 //             atomic per workgroup of 1,024 entries); the walks below read
 //             only these (a tenth of the entries in a mapping batch)
-//   hist      each workgroup of 512 threads takes chunks of 1,024 listed
+//   hist      each workgroup of 512 threads takes chunks of 512 listed
 //             splats of one view and counts, in an LDS histogram over that
 //             view's tiles, the keys they emit (each splat's tile rectangle
 //             in float64 from its float32 centre), then stores the whole
@@ -34,7 +34,8 @@
 //   order     optional: the tiles stably sorted by list length group,
 //             longest first (the launch order of the compositing grids)
 //
-// Views with more tiles than the LDS histogram holds are processed in tile
+// Small batches take a short path of five launches with the same results (see
+// run_bin_sort).  Views with more tiles than the LDS histogram holds are processed in tile
 // windows (one walk per window).  Nothing here needs a host synchronisation
 // unless the caller asks for the key count.
 #include "gs_internal.h"
@@ -45,15 +46,23 @@ namespace {
 
 constexpr int kBinThreads = 512;                         // threads of a binning workgroup
 constexpr int kBinWaves = kBinThreads / 64;
-constexpr int kWalkBatch = 2;                            // splats per binning thread
-constexpr int kBinChunk = kBinThreads * kWalkBatch;      // splats per binning chunk
-constexpr int kBinGrid = 32;                             // binning workgroups per view
+constexpr int kBinChunk = kBinThreads;                  // splats per binning chunk
+constexpr int kBinGrid = 64;                             // binning workgroups per view
 constexpr int kLdsTiles = 8192;                          // largest LDS histogram (tiles)
 constexpr int kSegShort = 1024;                          // longest list of the wavefront sort
 constexpr int kSegLong = 4096;                           // longest list of the workgroup sort
 constexpr int kSortThreads = 512;                        // threads of a sort workgroup
 constexpr int kSortWaves = kSortThreads / 64;
-constexpr int kLongSlots = 256;                          // sort workgroups that take the long lists
+constexpr int kLongSlots = 512;                          // most sort workgroups that take the long lists
+
+// The short path (see run_bin_sort): at most kFewGaussians Gaussians,
+// kFewEntries (view, Gaussian) entries and kFewTiles tiles.
+constexpr int kFewThreads = 256;                         // threads of its binning workgroups
+constexpr int64_t kFewEntries = 1 << 20;
+constexpr int64_t kFewGaussians = 1 << 18;
+constexpr int kFewTiles = 16384;
+constexpr int kFewRows = 256;                            // most chunks of a view
+constexpr int kFewColWaves = 16;                         // wavefronts that share a column's rows
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 
@@ -108,10 +117,10 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
 
 // Per wavefront: its 64 entries' key ranges and rectangles while it walks them.
 struct WalkLds {
-  uint4 rect[kBinWaves][64];   // first key in the wave's run, first tile (view-local), width, tiles per row
-  uint32_t ent[kBinWaves][64];
-  uint32_t dep[kBinWaves][64];   // float32 depth bits (emission only)
-  uint32_t mark[kBinWaves][64];
+  uint4 rect[64];      // first key in the wave's run, first tile (view-local), width, tiles per row
+  uint32_t ent[64];
+  uint32_t dep[64];    // float32 depth bits (emission only)
+  uint32_t mark[64];
 };
 
 // q = jj / w for jj < 2^20 and 1 <= w < 2^11: a float reciprocal estimate
@@ -123,84 +132,82 @@ __device__ __forceinline__ uint32_t div_small(uint32_t jj, uint32_t w) {
   return q;
 }
 
-// Calls op(view-local tile, entry, depth bits) once for every key that the
-// splats j0 .. j0 + kBinChunk of a view's compacted list (count splats in
-// all) emit.  Each thread takes kWalkBatch splats (stride kBinThreads) and
-// issues their loads together; then, per splat slot, each wavefront walks
-// its 64 splats' keys 64 at a time, every lane taking the key at its
-// position and finding the splat that owns it as the last splat whose first
-// key is at or before it (a prefix maximum over start marks), so large
-// rectangles spread over the lanes.
+// A splat's keys: their number, and its first tile | rectangle width << 21 (a
+// view has at most 2^20 tiles, a rectangle at most 1,024 columns).
+struct SplatKeys {
+  uint32_t cnt, rect;
+};
+
+__device__ __forceinline__ SplatKeys splat_keys(const uint4& c, const ViewInfo& vi) {
+  SplatKeys k{0u, 1u << 21};
+  Rect rc;
+  if (tile_rect(__uint_as_float(c.x), __uint_as_float(c.y), (int32_t)c.z, vi.width, vi.height, rc)) {
+    k.cnt = (uint32_t)((rc.x1 - rc.x0) * (rc.y1 - rc.y0));
+    k.rect = (uint32_t)(rc.y0 * vi.tiles_x + rc.x0) | ((uint32_t)(rc.x1 - rc.x0) << 21);
+  }
+  return k;
+}
+
+// Calls op(view-local tile, entry, depth bits) once for every key of a
+// wavefront's 64 splats (one per lane; cnt 0: none): the wavefront walks the
+// keys 64 at a time, every lane taking the key at its position and finding the
+// splat that owns it as the last splat whose first key is at or before it (a
+// prefix maximum over start marks), so large rectangles spread over the lanes.
+template <bool kDepth, typename Op>
+__device__ __forceinline__ void walk_wave(const SplatKeys& k, uint32_t id, uint32_t dep,
+                                          const ViewInfo& vi, WalkLds& L, Op op) {
+  const uint32_t lane = lane_id();
+  const uint32_t inc = wave_prefix_sum(k.cnt);
+  const uint32_t start = inc - k.cnt;
+  const uint32_t wend = __builtin_amdgcn_readlane(inc, 63);
+  if (wend == 0) return;   // uniform within the wavefront
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  L.rect[lane] = make_uint4(start, k.rect & 0x1FFFFFu, k.rect >> 21, (uint32_t)vi.tiles_x);
+  if constexpr (kDepth) {
+    L.ent[lane] = id;
+    L.dep[lane] = dep;
+  }
+  uint32_t carry = 0;   // 1 + lane of the entry owning the position before the window
+  for (uint32_t w0 = 0; w0 < wend; w0 += 64) {
+    L.mark[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    if (k.cnt > 0 && start >= w0 && start - w0 < 64) L.mark[start - w0] = lane + 1;
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    const uint32_t m = wave_prefix_max(max(L.mark[lane], carry));
+    carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
+    const uint32_t pos = w0 + lane;
+    if (pos < wend) {   // then m >= 1: the owner's first key is at or before pos
+      const uint4 rc = L.rect[m - 1];
+      const uint32_t jj = pos - rc.x;
+      const uint32_t row = div_small(jj, rc.z);
+      if constexpr (kDepth)
+        op(rc.y + row * rc.w + (jj - row * rc.z), L.ent[m - 1], L.dep[m - 1]);
+      else
+        op(rc.y + row * rc.w + (jj - row * rc.z), 0u, 0u);
+    }
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  }
+}
+
+// walk_wave over splats j0 .. j0 + kBinChunk of a view's compacted list (count
+// splats in all), one per thread.  (Two per thread, 1,024 to a chunk, left the
+// chip short of wavefronts: the whole binning took 124 us instead of 109 for 32
+// views of 640x480 over 200,000 Gaussians, 81 instead of 73 for 12.)
 template <bool kDepth, typename Op>
 __device__ __forceinline__ void walk_keys(const uint4* __restrict__ rec,
                                           const uint32_t* __restrict__ ids, uint32_t count,
-                                          uint32_t j0, const ViewInfo& vi, WalkLds& L, Op op) {
-  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
-  // all loads of the batch first, from clamped indices (no branches between
-  // them, so they are in flight together); slots past the list get radius 0
-  uint4 c[kWalkBatch];
-  uint32_t id[kWalkBatch];
-#pragma unroll
-  for (int q = 0; q < kWalkBatch; ++q) {
-    const uint32_t j = j0 + q * kBinThreads + threadIdx.x;
-    const uint32_t jc = j < count ? j : count - 1;
-    c[q] = rec[jc];
-    if constexpr (kDepth) id[q] = ids[jc];
-    if (j >= count) c[q].z = 0u;
-  }
-  // per entry: key count, and first tile | rectangle width << 21 (a view
-  // has at most 2^20 tiles, a rectangle at most 1,024 columns)
-  uint32_t cnt[kWalkBatch], rect[kWalkBatch], dep[kWalkBatch];
-#pragma unroll
-  for (int q = 0; q < kWalkBatch; ++q) {
-    Rect rc;
-    cnt[q] = 0;
-    rect[q] = 1u << 21;
-    dep[q] = 0;
-    if (tile_rect(__uint_as_float(c[q].x), __uint_as_float(c[q].y), (int32_t)c[q].z, vi.width,
-                  vi.height, rc)) {
-      cnt[q] = (uint32_t)((rc.x1 - rc.x0) * (rc.y1 - rc.y0));
-      rect[q] = (uint32_t)(rc.y0 * vi.tiles_x + rc.x0) | ((uint32_t)(rc.x1 - rc.x0) << 21);
-      if constexpr (kDepth) dep[q] = c[q].w;
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < kWalkBatch; ++q) {
-    const uint32_t inc = wave_prefix_sum(cnt[q]);
-    const uint32_t start = inc - cnt[q];
-    const uint32_t wend = __builtin_amdgcn_readlane(inc, 63);
-    if (wend == 0) continue;   // uniform within the wavefront
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    L.rect[w][lane] = make_uint4(start, rect[q] & 0x1FFFFFu, rect[q] >> 21, (uint32_t)vi.tiles_x);
-    if constexpr (kDepth) {
-      L.ent[w][lane] = id[q];
-      L.dep[w][lane] = dep[q];
-    }
-    uint32_t carry = 0;   // 1 + lane of the entry owning the position before the window
-    for (uint32_t w0 = 0; w0 < wend; w0 += 64) {
-      L.mark[w][lane] = 0;
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-      if (cnt[q] > 0 && start >= w0 && start - w0 < 64) L.mark[w][start - w0] = lane + 1;
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-      const uint32_t m = wave_prefix_max(max(L.mark[w][lane], carry));
-      carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
-      const uint32_t pos = w0 + lane;
-      if (pos < wend) {   // then m >= 1: the owner's first key is at or before pos
-        const uint4 rc = L.rect[w][m - 1];
-        const uint32_t jj = pos - rc.x;
-        const uint32_t row = div_small(jj, rc.z);
-        if constexpr (kDepth)
-          op(rc.y + row * rc.w + (jj - row * rc.z), L.ent[w][m - 1], L.dep[w][m - 1]);
-        else
-          op(rc.y + row * rc.w + (jj - row * rc.z), 0u, 0u);
-      }
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    }
-  }
+                                          uint32_t j0, const ViewInfo& vi, WalkLds* L, Op op) {
+  const uint32_t j = j0 + threadIdx.x;
+  const uint32_t jc = j < count ? j : count - 1;
+  uint4 c = rec[jc];
+  uint32_t id = 0;
+  if constexpr (kDepth) id = ids[jc];
+  if (j >= count) c.z = 0u;   // past the list: radius 0, no keys
+  walk_wave<kDepth>(splat_keys(c, vi), id, c.w, vi, L[threadIdx.x >> 6], op);
 }
 
 // ---------------------------------------------------------------------------
@@ -287,7 +294,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_hist_kernel(const uint4* __re
                                                                int lds_tiles,
                                                                uint32_t* __restrict__ matrix) {
   extern __shared__ uint32_t s_hist[];
-  __shared__ WalkLds L;
+  __shared__ WalkLds L[kBinWaves];
   const int v = blockIdx.y;
   const ViewInfo& vi = vt.v[v];
   const uint32_t count = list_count[v];
@@ -461,7 +468,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_emit_kernel(
     const uint32_t* __restrict__ matrix, const uint32_t* __restrict__ starts,
     const uint64_t* __restrict__ total, int64_t capacity, uint64_t* __restrict__ staged) {
   extern __shared__ uint32_t s_slot[];
-  __shared__ WalkLds L;
+  __shared__ WalkLds L[kBinWaves];
   if (*total > (uint64_t)capacity) return;
   const int v = blockIdx.y;
   const ViewInfo& vi = vt.v[v];
@@ -681,7 +688,7 @@ __device__ void radix_segment_sort(uint64_t* a, uint64_t* b, int64_t len, uint32
   }
 }
 
-// Grid kLongSlots + T / kSortWaves.  The first kLongSlots workgroups take
+// Grid long_slots + T / kSortWaves.  The first long_slots workgroups take
 // the queued lists longer than kSegShort (all wavefronts of a workgroup up to
 // kSegLong pairs, else the radix sort, whose pair buffers are `staged` itself
 // and `spare`); they are dispatched first, so the long lists run beside the
@@ -695,13 +702,14 @@ __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(const uint32_t* 
                                                                 K* __restrict__ keys,
                                                                 uint32_t* __restrict__ vals,
                                                                 const uint32_t* __restrict__ long_list,
-                                                                const uint32_t* __restrict__ n_long) {
+                                                                const uint32_t* __restrict__ n_long,
+                                                                int long_slots) {
   __shared__ uint64_t s_mem[kSegLong + 128];   // pairs, or the radix sort's digit counts
-  if (blockIdx.x < (unsigned)kLongSlots) {
+  if (blockIdx.x < (unsigned)long_slots) {
     uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_mem + kSegLong);
     uint32_t* s_wdig = reinterpret_cast<uint32_t*>(s_mem);
     const uint32_t count = *n_long;
-    for (uint32_t q = blockIdx.x; q < count; q += kLongSlots) {
+    for (uint32_t q = blockIdx.x; q < count; q += (uint32_t)long_slots) {
       const uint32_t tile = long_list[q];
       const uint32_t s = ranges[2 * (int64_t)tile], e = ranges[2 * (int64_t)tile + 1];
       const int64_t len = (int64_t)e - (int64_t)s;
@@ -718,7 +726,7 @@ __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(const uint32_t* 
     }
     return;
   }
-  const int tile = (int)(blockIdx.x - kLongSlots) * kSortWaves + (int)(threadIdx.x >> 6);
+  const int tile = (int)(blockIdx.x - long_slots) * kSortWaves + (int)(threadIdx.x >> 6);
   if (tile >= n_tiles) return;
   const uint32_t s = ranges[2 * (int64_t)tile], e = ranges[2 * (int64_t)tile + 1];
   const int64_t len = (int64_t)e - (int64_t)s;   // 0 for every tile on overflow
@@ -852,6 +860,267 @@ __global__ __launch_bounds__(kOrderBlock) void order_scatter_kernel(
     order[blk[blockIdx.x * kOrderGroups + g] + rank] = (uint32_t)(blockIdx.x * kOrderBlock + threadIdx.x);
 }
 
+// ---------------------------------------------------------------------------
+// the short path: few entries, few tiles
+// ---------------------------------------------------------------------------
+
+// Calls walk_wave for a chunk's splats, dealt evenly to the workgroup's
+// wavefronts: load(j) gives splat j's record and entry.
+template <bool kDepth, typename Load, typename Op>
+__device__ __forceinline__ void few_walk(uint32_t count, const ViewInfo& vi, WalkLds* L, Load load,
+                                         Op op) {
+  constexpr uint32_t kWaves = kFewThreads / 64;
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  const uint32_t per = (count + kWaves - 1) / kWaves;
+  const uint32_t end = min(count, (w + 1) * per);
+  for (uint32_t j0 = w * per; j0 < end; j0 += 64) {
+    uint32_t id = 0;
+    uint4 c = make_uint4(0u, 0u, 0u, 0u);
+    SplatKeys k{0u, 1u << 21};
+    if (j0 + lane < end) {
+      c = load(j0 + lane, id);
+      k = splat_keys(c, vi);
+    }
+    walk_wave<kDepth>(k, id, c.w, vi, L[w], op);
+  }
+}
+
+// Grid (chunks, views), chunks of kEntries entries: the chunk's splats that
+// touch a tile go to its part of the list (and their number to few_count), and
+// the keys they emit are counted per tile into the chunk's row of the matrix.
+// Chunk b takes every gridDim.x-th run of 64 entries from run b on: neighbours
+// in a map are neighbours in space, and chunks of consecutive entries would be
+// all visible or not at all.
+template <int kEntries>
+__global__ __launch_bounds__(kFewThreads) void few_gather_kernel(
+    const float2* __restrict__ xy, const int32_t* __restrict__ radius,
+    const float4* __restrict__ rd, const uint32_t* __restrict__ stored, int n, ViewTable vt,
+    uint32_t* __restrict__ few_count, uint4* __restrict__ rec, uint32_t* __restrict__ ids,
+    uint32_t* __restrict__ matrix) {
+  constexpr int kWaves = kFewThreads / 64;
+  constexpr int kItems = (kEntries + kFewThreads - 1) / kFewThreads;
+  extern __shared__ uint32_t s_hist[];
+  __shared__ WalkLds L[kWaves];
+  __shared__ uint4 s_rec[kEntries];
+  __shared__ uint32_t s_wave[kWaves];
+  const int v = blockIdx.y;
+  const ViewInfo& vi = vt.v[v];
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  const int vtiles = vi.tiles_x * vi.tiles_y;
+  bool keep[kItems];
+  uint4 c[kItems];
+  int64_t entry[kItems];
+  uint32_t mine = 0;
+#pragma unroll
+  for (int q = 0; q < kItems; ++q) {
+    const int run = q * kWaves + (int)w;   // of the chunk's kEntries / 64
+    const int64_t i = ((int64_t)run * gridDim.x + blockIdx.x) * 64 + lane;
+    const bool mine_q = run < kEntries / 64 && i < n;
+    entry[q] = (int64_t)v * n + (mine_q ? i : 0);
+    const int32_t r = radius[entry[q]];
+    const uint32_t x = stored ? stored[entry[q]] : (uint32_t)max(r, 0);
+    const float2 m = xy[entry[q]];
+    c[q] = make_uint4(__float_as_uint(m.x), __float_as_uint(m.y), (uint32_t)r,
+                      __float_as_uint(rd[entry[q]].w));
+    keep[q] = mine_q && x > 0u;
+    mine += keep[q] ? 1u : 0u;
+  }
+  for (int t = threadIdx.x; t < vtiles; t += kFewThreads) s_hist[t] = 0u;
+  const uint32_t inc = wave_prefix_sum(mine);
+  if (lane == 63) s_wave[w] = inc;
+  __syncthreads();
+  uint32_t pos = inc - mine, count = 0;
+#pragma unroll
+  for (uint32_t k = 0; k < kWaves; ++k) {
+    pos += k < w ? s_wave[k] : 0u;
+    count += s_wave[k];
+  }
+  const int64_t seg = ((int64_t)v * gridDim.x + blockIdx.x) * kEntries;
+#pragma unroll
+  for (int q = 0; q < kItems; ++q) {
+    if (keep[q]) {
+      s_rec[pos] = c[q];
+      rec[seg + pos] = c[q];
+      ids[seg + pos] = (uint32_t)entry[q];
+      ++pos;
+    }
+  }
+  if (threadIdx.x == 0) few_count[v * gridDim.x + blockIdx.x] = count;
+  __syncthreads();
+  few_walk<false>(count, vi, L, [&](uint32_t j, uint32_t&) { return s_rec[j]; },
+                  [&](uint32_t tile, uint32_t, uint32_t) { atomicAdd(&s_hist[tile], 1u); });
+  __syncthreads();
+  uint32_t* row = matrix + (int64_t)blockIdx.x * vt.n_tiles + vi.tile_base;
+  for (int t = threadIdx.x; t < vtiles; t += kFewThreads) row[t] = s_hist[t];
+}
+
+// Grid T / 64: the wavefronts of a workgroup share the rows of 64 columns
+// (kFewRows / kFewColWaves each, all in registers): every column's exclusive
+// scan down the rows, in place, and its total.
+__global__ __launch_bounds__(64 * kFewColWaves) void few_column_kernel(
+    uint32_t* __restrict__ matrix, int rows, int n_tiles, uint32_t* __restrict__ counts) {
+  constexpr int kOwn = kFewRows / kFewColWaves;
+  __shared__ uint32_t s_sum[kFewColWaves][64];
+  const int lane = lane_id(), w = threadIdx.x >> 6;
+  const int t = (int)blockIdx.x * 64 + lane;
+  const int per = (rows + kFewColWaves - 1) / kFewColWaves;
+  const int r0 = w * per, r1 = min(rows, r0 + per);
+  uint32_t x[kOwn], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k)
+    x[k] = r0 + k < r1 && t < n_tiles ? matrix[(int64_t)(r0 + k) * n_tiles + t] : 0u;
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) sum += x[k];
+  s_sum[w][lane] = sum;
+  __syncthreads();
+  if (t >= n_tiles) return;
+  uint32_t run = 0;
+  for (int k = 0; k < w; ++k) run += s_sum[k][lane];
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    if (r0 + k < r1) matrix[(int64_t)(r0 + k) * n_tiles + t] = run;
+    run += x[k];
+  }
+  if (w == kFewColWaves - 1) counts[t] = run;
+}
+
+// One workgroup, at most kFewTiles tiles: the segments and the key count (as
+// bin_scan_down_kernel writes them), the queue of long lists, cleared tile
+// counters and, when wanted, the tile order (as the order_* kernels write it).
+__global__ __launch_bounds__(1024) void few_scan_kernel(
+    const uint32_t* __restrict__ counts, int n_tiles, int64_t capacity,
+    uint32_t* __restrict__ ranges, uint32_t* __restrict__ starts, uint64_t* __restrict__ total,
+    uint32_t* __restrict__ n_keys, uint32_t* __restrict__ long_list,
+    uint32_t* __restrict__ n_long, uint32_t* __restrict__ queue, uint32_t* __restrict__ order) {
+  constexpr int kPer = kFewTiles / 1024;   // tile c 1024 + thread, c < kPer
+  constexpr int kWaves = 16;
+  constexpr int kCells = kOrderGroups * kPer * kWaves;   // (group, c, wave), longest group first
+  __shared__ uint32_t s_tot[kPer * kWaves];   // per (c, wave): keys, then keys before it
+  __shared__ uint32_t s_cell[kCells];
+  __shared__ uint32_t s_wave[kWaves];
+  __shared__ uint64_t s_all;
+  __shared__ uint32_t s_long;
+  const uint32_t lane = lane_id(), w = threadIdx.x >> 6;
+  if (queue)
+    for (int k = threadIdx.x; k < GS_QUEUE_WORDS; k += 1024) queue[k] = 0u;
+  if (threadIdx.x == 0) s_long = 0u;
+  for (int k = threadIdx.x; k < kCells; k += 1024) s_cell[k] = 0u;
+  uint32_t cnt[kPer], inc[kPer];
+#pragma unroll
+  for (int c = 0; c < kPer; ++c) {
+    const int t = c * 1024 + (int)threadIdx.x;
+    cnt[c] = t < n_tiles ? counts[t] : 0u;
+  }
+#pragma unroll
+  for (int c = 0; c < kPer; ++c) {
+    inc[c] = wave_prefix_sum(cnt[c]);
+    if (lane == 63) s_tot[c * kWaves + w] = inc[c];
+  }
+  __syncthreads();
+  if (w == 0) {
+    constexpr int kOwn = kPer * kWaves / 64;   // totals per lane (below 2^26 together)
+    uint32_t a[kOwn], sum = 0;
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) sum += a[k] = s_tot[kOwn * lane + k];
+    const uint64_t p = wave_inclusive_scan<uint64_t>(sum);
+    uint32_t run = (uint32_t)p - sum;   // exact whenever the keys fit the capacity's 32 bits
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      s_tot[kOwn * lane + k] = run;
+      run += a[k];
+    }
+    if (lane == 63) {
+      s_all = p;
+      *total = p;
+      *n_keys = p > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)p;
+    }
+  }
+  __syncthreads();
+  const bool ok = s_all <= (uint64_t)capacity;
+  uint32_t rank[kPer];
+#pragma unroll
+  for (int c = 0; c < kPer; ++c) {
+    const int t = c * 1024 + (int)threadIdx.x;
+    if (c * 1024 >= n_tiles) break;   // uniform
+    const uint32_t len = ok ? cnt[c] : 0u;
+    const uint32_t st = s_tot[c * kWaves + w] + inc[c] - cnt[c];
+    if (t < n_tiles) {
+      ranges[2 * (int64_t)t] = len ? st : 0u;
+      ranges[2 * (int64_t)t + 1] = len ? st + len : 0u;
+      starts[t] = st;
+      if (len > (uint32_t)kSegShort) long_list[atomicAdd(&s_long, 1u)] = (uint32_t)t;
+    }
+    // the lanes of this wavefront whose tiles share the length group
+    const uint32_t g = (uint32_t)length_group(len);
+    uint64_t peers = __ballot(t < n_tiles);
+#pragma unroll
+    for (int b = 0; b < 5; ++b) {
+      const uint64_t m = __ballot((g >> b) & 1u);
+      peers &= ((g >> b) & 1u) ? m : ~m;
+    }
+    rank[c] = (uint32_t)__popcll(peers & ((uint64_t(1) << lane) - 1));
+    if (t < n_tiles && rank[c] == 0)
+      s_cell[((kOrderGroups - 1 - g) * kPer + c) * kWaves + w] = (uint32_t)__popcll(peers);
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *n_long = s_long;
+  if (!order) return;
+  constexpr int kOwnCells = kCells / 1024;
+  uint32_t cell[kOwnCells], mine = 0;
+#pragma unroll
+  for (int k = 0; k < kOwnCells; ++k) {
+    cell[k] = s_cell[kOwnCells * threadIdx.x + k];
+    mine += cell[k];
+  }
+  const uint32_t cinc = wave_prefix_sum(mine);
+  if (lane == 63) s_wave[w] = cinc;
+  __syncthreads();
+  uint32_t off = cinc - mine;
+  for (uint32_t k = 0; k < w; ++k) off += s_wave[k];
+#pragma unroll
+  for (int k = 0; k < kOwnCells; ++k) {
+    s_cell[kOwnCells * threadIdx.x + k] = off;
+    off += cell[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kPer; ++c) {
+    const int t = c * 1024 + (int)threadIdx.x;
+    if (c * 1024 >= n_tiles) break;
+    if (t < n_tiles) {
+      const uint32_t g = (uint32_t)length_group(ok ? cnt[c] : 0u);
+      order[s_cell[((kOrderGroups - 1 - g) * kPer + c) * kWaves + w] + rank[c]] = (uint32_t)t;
+    }
+  }
+}
+
+// Grid (chunks, views): bin_emit_kernel on the short path's chunks.
+__global__ __launch_bounds__(kFewThreads) void few_emit_kernel(
+    const uint4* __restrict__ rec, const uint32_t* __restrict__ ids,
+    const uint32_t* __restrict__ few_count, int entries, ViewTable vt,
+    const uint32_t* __restrict__ matrix, const uint32_t* __restrict__ starts,
+    const uint64_t* __restrict__ total, int64_t capacity, uint64_t* __restrict__ staged) {
+  extern __shared__ uint32_t s_slot[];
+  __shared__ WalkLds L[kFewThreads / 64];
+  const int v = blockIdx.y;
+  const uint32_t count = few_count[v * gridDim.x + blockIdx.x];
+  if (count == 0 || *total > (uint64_t)capacity) return;
+  const ViewInfo& vi = vt.v[v];
+  const int vtiles = vi.tiles_x * vi.tiles_y;
+  const uint32_t* row = matrix + (int64_t)blockIdx.x * vt.n_tiles + vi.tile_base;
+  for (int t = threadIdx.x; t < vtiles; t += kFewThreads) s_slot[t] = starts[vi.tile_base + t] + row[t];
+  const int64_t seg = ((int64_t)v * gridDim.x + blockIdx.x) * entries;
+  __syncthreads();
+  few_walk<true>(count, vi, L,
+                 [&](uint32_t j, uint32_t& id) {
+                   id = ids[seg + j];
+                   return rec[seg + j];
+                 },
+                 [&](uint32_t tile, uint32_t ent, uint32_t dep) {
+                   staged[atomicAdd(&s_slot[tile], 1u)] = ((uint64_t)dep << 32) | ent;
+                 });
+}
+
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int64_t bin_chunks(int64_t n) { return (n + kBinChunk - 1) / kBinChunk; }   // at most
@@ -877,12 +1146,22 @@ BinSortPlan make_bin_sort_plan(int64_t n, const ViewTable& vt, int64_t capacity)
     P.max_view_tiles = std::max(P.max_view_tiles, vt.v[v].tiles_x * vt.v[v].tiles_y);
     P.lds_tiles = std::max(P.lds_tiles, std::min(kLdsTiles, vt.v[v].tiles_x * vt.v[v].tiles_y));
   }
+  P.few_entries = 0;
+  size_t list = (size_t)P.n_entries;   // compacted splats
+  if (n > 0 && n <= kFewGaussians && P.n_entries <= kFewEntries && vt.n_tiles <= kFewTiles &&
+      P.max_view_tiles <= kLdsTiles) {
+    // the smallest chunks that number at most about 256 over all views: a small
+    // map fills the GPU, a larger one keeps the matrix small
+    P.few_entries = P.n_entries <= 256 * 64 ? 64 : P.n_entries <= 256 * 256 ? 256 : 1024;
+    P.chunks = (n + P.few_entries - 1) / P.few_entries;
+    list = (size_t)P.chunks * P.few_entries * vt.n_views;
+  }
   const size_t nt = sizeof(uint32_t) * (size_t)std::max(vt.n_tiles, 1);
   size_t off = 0;
   P.off_matrix = off;    off += align_up(sizeof(uint32_t) * (size_t)P.chunks * (size_t)vt.n_tiles);
-  P.off_list = off;      off += align_up(sizeof(uint4) * (size_t)P.n_entries);      // compacted splats
-  P.off_ids = off;       off += align_up(sizeof(uint32_t) * (size_t)P.n_entries);   // their entries
-  P.off_list_count = off; off += align_up(sizeof(uint32_t) * GS_MAX_VIEWS);
+  P.off_list = off;      off += align_up(sizeof(uint4) * list);      // compacted splats
+  P.off_ids = off;       off += align_up(sizeof(uint32_t) * list);   // their entries
+  P.off_list_count = off; off += align_up(sizeof(uint32_t) * std::max<size_t>(GS_MAX_VIEWS, P.few_entries ? (size_t)P.chunks * vt.n_views : 0));
   P.off_counts = off;    off += align_up(nt);   // keys per tile
   P.off_starts = off;    off += align_up(nt);   // first slot of every tile's segment
   P.off_long = off;      off += align_up(nt);   // tiles whose lists the long grid sorts
@@ -930,25 +1209,50 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
   const unsigned tblocks = (unsigned)((T + 255) / 256);
   const dim3 bin_grid((unsigned)std::min<int64_t>(kBinGrid, std::max<int64_t>(P.chunks, 1)),
                       (unsigned)vt.n_views);
-  // 1. the splats that touch a tile, per view; keys per (chunk, tile), per
-  // tile, the segments and the key count
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, s, list_count, 0u,
-                     (int64_t)vt.n_views);
-  if (n > 0) {
-    hipLaunchKernelGGL(bin_compact_kernel, dim3((unsigned)((n + kCompactChunk - 1) / kCompactChunk),
-                       (unsigned)vt.n_views), dim3(256), 0, s, xy, p.radius, rd, p.tiles, n,
-                       list_count, list, ids);
-    hipLaunchKernelGGL(bin_hist_kernel, bin_grid, dim3(kBinThreads), lds, s, list, list_count, n,
-                       vt, P.lds_tiles, matrix);
+  // Short path: few entries and tiles, where launches and idle CUs are most of
+  // the time.  Fixed chunks need no list shared by a view (its counter, clearing
+  // and compaction), and one workgroup does the scans and the order: five
+  // launches instead of eleven.  Whole call, short | general: 2,000 entries on
+  // 80 tiles 23 | 41 us, 65,536 on 1,200 28 | 53, 262,144 on 3,225 38 | 56,
+  // 600,000 on 14,400 58 | 105.  The limits are where the two meet (4 x 262,144
+  // entries on 12,900 tiles: 64 | 67) and where one workgroup holds the tiles and
+  // the column kernel a column's 256 rows.
+  const bool few = P.few_entries != 0;
+  const dim3 few_grid((unsigned)P.chunks, (unsigned)vt.n_views);
+  if (few) {
+#define GS_GATHER(E)                                                                          \
+  hipLaunchKernelGGL(few_gather_kernel<E>, few_grid, dim3(kFewThreads), lds, s, xy, p.radius, rd, \
+                     p.tiles, (int)n, vt, list_count, list, ids, matrix)
+    if (P.few_entries == 64) GS_GATHER(64);
+    else if (P.few_entries == 256) GS_GATHER(256);
+    else GS_GATHER(1024);
+#undef GS_GATHER
+    hipLaunchKernelGGL(few_column_kernel, dim3((unsigned)((T + 63) / 64)), dim3(64 * kFewColWaves),
+                       0, s, matrix, (int)P.chunks, T, counts);
+    hipLaunchKernelGGL(few_scan_kernel, dim3(1), dim3(1024), 0, s, counts, T, P.capacity,
+                       bins.ranges, starts, total, bins.n_keys, long_list, n_long, bins.queue,
+                       bins.order);
+  } else {
+    // 1. the splats that touch a tile, per view; keys per (chunk, tile), per
+    // tile, the segments and the key count
+    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, s, list_count, 0u,
+                       (int64_t)vt.n_views);
+    if (n > 0) {
+      hipLaunchKernelGGL(bin_compact_kernel, dim3((unsigned)((n + kCompactChunk - 1) / kCompactChunk),
+                         (unsigned)vt.n_views), dim3(256), 0, s, xy, p.radius, rd, p.tiles, n,
+                         list_count, list, ids);
+      hipLaunchKernelGGL(bin_hist_kernel, bin_grid, dim3(kBinThreads), lds, s, list, list_count, n,
+                         vt, P.lds_tiles, matrix);
+    }
+    hipLaunchKernelGGL(bin_column_kernel, dim3((unsigned)((P.max_view_tiles + 255) / 256),
+                       (unsigned)vt.n_views), dim3(256), 0, s, matrix, list_count, vt, counts);
+    const int nsb = (T + kScanBlock - 1) / kScanBlock;
+    hipLaunchKernelGGL(bin_scan_reduce_kernel, dim3((unsigned)nsb), dim3(256), 0, s, counts, T,
+                       partial, n_long, bins.queue);
+    hipLaunchKernelGGL(bin_scan_down_kernel, dim3((unsigned)nsb), dim3(256), 0, s, counts, T,
+                       partial, nsb, P.capacity, bins.ranges, starts, total, bins.n_keys, long_list,
+                       n_long);
   }
-  hipLaunchKernelGGL(bin_column_kernel, dim3((unsigned)((P.max_view_tiles + 255) / 256),
-                     (unsigned)vt.n_views), dim3(256), 0, s, matrix, list_count, vt, counts);
-  const int nsb = (T + kScanBlock - 1) / kScanBlock;
-  hipLaunchKernelGGL(bin_scan_reduce_kernel, dim3((unsigned)nsb), dim3(256), 0, s, counts, T,
-                     partial, n_long, bins.queue);
-  hipLaunchKernelGGL(bin_scan_down_kernel, dim3((unsigned)nsb), dim3(256), 0, s, counts, T,
-                     partial, nsb, P.capacity, bins.ranges, starts, total, bins.n_keys, long_list,
-                     n_long);
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "bin count launch");
 
   bool empty = false;
@@ -971,20 +1275,27 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
   }
   // 2. placement into the segments, then each segment sorted by (depth, entry)
   if (n > 0 && !empty) {
-    hipLaunchKernelGGL(bin_emit_kernel, bin_grid, dim3(kBinThreads), lds, s, list, ids, list_count,
-                       n, vt, P.lds_tiles, matrix, starts, total, P.capacity, staged);
-    const unsigned sblocks = (unsigned)(kLongSlots + (T + kSortWaves - 1) / kSortWaves);
+    if (few)
+      hipLaunchKernelGGL(few_emit_kernel, few_grid, dim3(kFewThreads), lds, s, list, ids,
+                         list_count, P.few_entries, vt, matrix, starts, total,
+                         P.capacity, staged);
+    else
+      hipLaunchKernelGGL(bin_emit_kernel, bin_grid, dim3(kBinThreads), lds, s, list, ids,
+                         list_count, n, vt, P.lds_tiles, matrix, starts, total, P.capacity, staged);
+    const int long_slots = std::min(kLongSlots, T);
+    const unsigned sblocks = (unsigned)(long_slots + (T + kSortWaves - 1) / kSortWaves);
     if (bins.keys)
       hipLaunchKernelGGL(seg_sort_kernel<uint64_t>, dim3(sblocks), dim3(kSortThreads), 0, s,
-                         bins.ranges, T, staged, spare, bins.keys, bins.values, long_list, n_long);
+                         bins.ranges, T, staged, spare, bins.keys, bins.values, long_list, n_long,
+                         long_slots);
     else
       hipLaunchKernelGGL(seg_sort_kernel<uint32_t>, dim3(sblocks), dim3(kSortThreads), 0, s,
                          bins.ranges, T, staged, spare, (uint32_t*)nullptr, bins.values, long_list,
-                         n_long);
+                         n_long, long_slots);
   }
   // 3. launch order of the compositing grids (from the ranges; on overflow
   // they are all empty and this is the identity)
-  if (bins.order) {
+  if (bins.order && !few) {
     const int nblk = (T + kOrderBlock - 1) / kOrderBlock;
     hipLaunchKernelGGL(order_count_kernel, dim3((unsigned)nblk), dim3(kOrderBlock), 0, s,
                        bins.ranges, T, order_blk);

@@ -309,7 +309,8 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s
 struct BinSortPlan {
   int64_t n_entries;     // V * n
   int64_t capacity;
-  int64_t chunks;        // binning workgroups per view
+  int64_t chunks;        // rows of the chunk x tile matrix
+  int32_t few_entries;   // short path: entries per chunk (0: the general path)
   int32_t n_tiles;
   int32_t lds_tiles;     // LDS histogram bins (largest view, at most the LDS limit)
   int32_t max_view_tiles;

@@ -521,171 +521,282 @@ __global__ __launch_bounds__(256) void conv3x3_wgrad_kernel(
   }
 }
 
-// Weight gradient on spatial tiles: dW[tap][co][ci] = sum over pixels p of
-// dz[p][co] x[p + tap][ci] (dz masked by the ReLU of the layer's output).  A
-// workgroup owns COB output and 32 input channels and all nine taps, and
-// walks a run of 8 x 16-pixel tiles.  Per tile it stages dz transposed to
-// [channel][pixel] and the tile's 10 x 18 input patch transposed to
-// [channel][row][column] in three copies shifted by 0, 1 and 2 columns, so
-// that every tap's operand (8 consecutive pixels of one row per lane) is an
-// aligned 16-byte LDS read; the K dimension of the MFMAs is the tile's 128
-// pixels.  Wavefront w computes input-channel block w % 2 against output
-// blocks (w / 2) and (w / 2) + 2 (COB 64) or block w / 2 (COB 32), for the
-// nine taps.  Partial sums go to dW (and dbias) by float atomics at the end.
-constexpr int WT_H = 8, WT_W = 16, WT_PX = WT_H * WT_W;   // pixels of a tile
-constexpr int WX_H = WT_H + 2, WX_W = WT_W + 2;           // input patch
-constexpr int WZ_PITCH = WT_PX + 8;                       // dz^T row pitch (bf16)
-constexpr int WX_PITCH = WX_H * WT_W + 8;                 // per-channel pitch of a shifted copy
+// Weight gradient: dW[tap][co][ci] = sum over pixels p of dz[p][co] x[p + tap][ci]
+// (dz masked by the ReLU of the layer's output), the pixels being the K dimension
+// of the MFMAs.
+//
+// A workgroup owns 32 NCO output and 32 NCI input channels and all nine taps. It
+// walks down strips of the images, 32 pixels wide, 4 NR rows a step: the step's
+// new rows of dz and of the input (34 pixels) go to LDS as they lie in memory,
+// [pixel][32 channels], with 16-byte loads and writes; the input's rows stay in a
+// ring, so only columns are read twice (34 of 32). The ring and the two dz buffers
+// hold the next step beside this one: one barrier a step, the loads of the next
+// step in flight while this one is multiplied.
+//
+// The fragments (8 pixels of one channel per lane) come out of LDS by transposing
+// reads (ds_read_b64_tr_b16: four pixels of 16 channels per 16 lanes), so a tap is
+// an address offset, and nothing is transposed by the VALU or stored shifted. The
+// two 16-channel halves of a pixel swap places every four pixels, so the eight
+// pixels that a read takes at a time cover all banks.
+//
+// A wavefront takes one column of taps (dx) of one 32 x 32 channel pair and four
+// of the step's rows: 48 accumulator registers instead of the 144 of nine taps at
+// about the same LDS reads per MFMA, since an input row's fragments serve the
+// three taps of the column against three rows of dz held in registers.
+//
+// 4 x 640x480, 96 -> 32 channels: 147 us (402 MB needed, 85 at this card's copy
+// rate), 276 on 16 x 8 tiles transposed by the VALU with three shifted copies of
+// the input. 8 x 160x120, 128 -> 128: 88 us, 31 of them the closing adds, 160
+// with a row of taps per workgroup. What is left is issue and LDS latency at three
+// wavefronts per SIMD: without the loads 128 and 84 us, without the MFMAs 152 and
+// 78 (before the row halves met in LDS, which took 10 us off the first).
+constexpr int WG_W = 32, WG_XW = WG_W + 2;
+constexpr int WG_XPITCH = 40;                   // pixels per input row in LDS
+constexpr int WG_ZROW = WG_W * 64, WG_XROW = WG_XPITCH * 64;   // bytes per row and 32-channel group
+constexpr int WG_SKEW = 128;                    // between the groups of a pixel: other banks
 
-template <int COB>
-__global__ __launch_bounds__(256) void conv3x3_wgrad_patch_kernel(
+typedef short short4v __attribute__((ext_vector_type(4)));
+typedef short short8v __attribute__((ext_vector_type(8)));
+
+// Byte offset of 16-byte piece c (of 4) of pixel p of a row in LDS.
+__device__ __forceinline__ int wg_piece(int p, int c) {
+  return p * 64 + ((c ^ (((p >> 2) & 1) << 1)) << 4);
+}
+
+// Zeroes the bf16 elements of v whose mask element is <= 0 (as int16, -0 among
+// them: 0 - x saturates, so its sign is set exactly where x > 0).
+__device__ __forceinline__ uint32_t mask_word(uint32_t v, uint32_t mk) {
+  typedef short short2v __attribute__((ext_vector_type(2)));
+  const short2v m = __builtin_elementwise_sub_sat(short2v{0, 0}, __builtin_bit_cast(short2v, mk));
+  return v & __builtin_bit_cast(uint32_t, (short2v)(m >> (short)15));
+}
+
+// Fragment: this lane's channel (of the 16 at the address) at pixels 4 g .. 4 g
+// + 3 and 16 + 4 g .. of a 32-pixel row, g = lane / 16; dz and the input use
+// the same order of pixels.
+__device__ __forceinline__ bf16x8 wg_fragment(const char* p) {
+  using lds = __attribute__((address_space(3))) short4v*;
+  const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)p);
+  const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)(p + 16 * 64));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int NCO, int NCI, int NR>
+__global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_strip_kernel(
     ActView x1, ActView x2, ActView dz, ActView mask, int N, int H, int W, int cout, int cin,
-    int tiles_per_wg, float* __restrict__ dw, float* __restrict__ dbias) {
-  constexpr int NCO = COB / 32;                      // output 16-blocks per wavefront
-  // staging items: two horizontally adjacent pixels x 8 channels, so that
-  // the transposed LDS writes are 32-bit words, consecutive across a wave
-  constexpr int ZI = (COB / 8) * (WT_PX / 2);        // dz items of a tile
-  constexpr int ZIT = ZI / 256;                      // per thread
-  constexpr int XROW = WX_W / 2;                     // pixel pairs per patch row (9)
-  constexpr int XI = 4 * WX_H * XROW;                // input items (32 channels)
-  constexpr int XIT = (XI + 255) / 256;
-  __shared__ __attribute__((aligned(16))) uint16_t sZ[COB * WZ_PITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t sX[3 * 32 * WX_PITCH];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int tiles_x = (W + WT_W - 1) / WT_W, tiles_y = (H + WT_H - 1) / WT_H;
-  const int64_t ntiles = (int64_t)N * tiles_x * tiles_y;
-  const int co0 = blockIdx.y * COB, ci0 = blockIdx.z * 32;
-  const bool do_bias = dbias != nullptr && blockIdx.z == 0;
-  const bool masked = mask.p != nullptr;
-  const ActView none = {nullptr, 0, 0, 0};
-  const int ci_sub = wv & 1, co_blk = wv >> 1;
-  f32x4 acc[NCO][9];
-#pragma unroll
-  for (int c = 0; c < NCO; ++c)
-#pragma unroll
-    for (int u = 0; u < 9; ++u) acc[c][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  float bacc = 0.f;   // thread t < COB: bias gradient of output channel co0 + t
-  uint4 rz[ZIT][2], rm[ZIT][2], rx[XIT][2];
-  auto fetch = [&](int64_t tile) {
-    const int img = (int)(tile / (tiles_x * tiles_y));
-    const int trem = (int)(tile - (int64_t)img * tiles_x * tiles_y);
-    const int ty0 = (trem / tiles_x) * WT_H, tx0 = (trem % tiles_x) * WT_W;
-#pragma unroll
-    for (int u = 0; u < ZIT; ++u) {            // item: channels 8 (i / 64), pixels 2 (i % 64) + 0, 1
-      const int i = t + 256 * u;
-      const int cg = i >> 6, p = 2 * (i & 63);
-      const int oy = ty0 + p / WT_W, ox = tx0 + p % WT_W;
-      const int64_t pix = ((int64_t)img * H + oy) * W + ox;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bool inb = oy < H && ox + h < W;
-        rz[u][h] = load8(dz, none, none, pix + h, inb, co0 + 8 * cg);
-        if (masked) rm[u][h] = load8(mask, none, none, pix + h, inb, co0 + 8 * cg);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < XIT; ++u) {            // item: channels 8 (i / 90), patch row, pixel pair
-      const int i = t + 256 * u;
-      const int cg = i / (WX_H * XROW), pr = i % (WX_H * XROW);
-      const int py = pr / XROW, px = 2 * (pr % XROW);
-      const int sy = ty0 + py - 1, sx = tx0 + px - 1;
-      const int64_t pix = ((int64_t)img * H + sy) * W + sx;
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bool inb = i < XI && sy >= 0 && sy < H && sx + h >= 0 && sx + h < W;
-        rx[u][h] = load8(x1, x2, none, pix + h, inb, ci0 + 8 * cg);
-      }
-    }
+    int n_pairs, int ci_groups, int steps_per_wg, float* __restrict__ dw,
+    float* __restrict__ dbias) {
+  constexpr int NT = 64 * 3 * NCO * NCI * NR;
+  constexpr int SR = 4 * NR;                            // rows per step
+  constexpr int RING = 2 * SR + 2;                      // input rows held
+  constexpr int ZP = 4 * NCO, XP = 4 * NCI;             // 16-byte pieces per pixel
+  static_assert(NT % ZP == 0 && NT % XP == 0, "a thread's pieces share their channels");
+  constexpr int ZIT = (SR * WG_W * ZP + NT - 1) / NT;
+  constexpr int XIT = (SR * WG_XW * XP + NT - 1) / NT;
+  constexpr int HIT = (2 * WG_XW * XP + NT - 1) / NT;   // the two rows above a run or strip
+  constexpr int ZGROUP = 2 * SR * WG_ZROW + WG_SKEW, XGROUP = RING * WG_XROW + WG_SKEW;
+  __shared__ __attribute__((aligned(16))) char s_z[NCO * ZGROUP];
+  __shared__ __attribute__((aligned(16))) char s_x[NCI * XGROUP];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  // all channel pairs of a run of steps on one XCD (workgroups go round the eight
+  // of them), close in time: what they share comes from its L2
+  const int slot = (int)blockIdx.x >> 3;
+  const int run = (slot / n_pairs) * 8 + ((int)blockIdx.x & 7), pair = slot % n_pairs;
+  const int co0 = (pair / ci_groups) * 32 * NCO, ci0 = (pair % ci_groups) * 32 * NCI;
+  const int strips = (W + WG_W - 1) / WG_W, strip_steps = (H + SR - 1) / SR;
+  const int n_steps = N * strips * strip_steps;
+  const int k_beg = run * steps_per_wg, k_end = min(n_steps, k_beg + steps_per_wg);
+  if (k_beg >= k_end) return;   // the whole workgroup
+
+  // this thread's pieces: channels 8 zc .. of dz (and mask), 8 xc .. of the input
+  const int zc = t % ZP, xc = t % XP;
+  const bool z_ok = co0 + 8 * zc < cout;
+  const uint16_t* zp = dz.p + dz.offset + co0 + 8 * zc;
+  const uint16_t* mp = mask.p ? mask.p + mask.offset + co0 + 8 * zc : nullptr;
+  const int xch = ci0 + 8 * xc;
+  const bool x_ok = xch < cin, from_1 = xch < x1.c;
+  const uint16_t* xp = from_1 ? x1.p + x1.offset + xch : x2.p + x2.offset + (xch - x1.c);
+  const int x_stride = from_1 ? x1.stride : x2.stride;
+  char* z_dst = s_z + (zc >> 2) * ZGROUP;
+  char* x_dst = s_x + (xc >> 2) * XGROUP;
+  int img = 0, tx0 = 0, r0 = 0;   // of the step: image, first column, first row
+  auto locate = [&](int k) {
+    const int strip = k / strip_steps;
+    img = strip / strips;
+    tx0 = (strip - img * strips) * WG_W;
+    r0 = (k - strip * strip_steps) * SR;
   };
-  // 32-bit word e of two pixels' 8-channel pieces: (pixel 0, pixel 1) of channel e
-  auto pair_word = [](const uint4& a, const uint4& b, int e) -> uint32_t {
-    const uint32_t wa[4] = {a.x, a.y, a.z, a.w}, wb[4] = {b.x, b.y, b.z, b.w};
-    const uint32_t lo = (wa[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-    const uint32_t hi = (wb[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-    return lo | (hi << 16);
+  // piece p of 34-pixel input rows from row r on (rows of the image only)
+  auto load_x = [&](int p, int rows, int r) {
+    const int i = p / WG_XW, sy = r + i, sx = tx0 + (p - i * WG_XW) - 1;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (x_ok && i < rows && (unsigned)sy < (unsigned)H && (unsigned)sx < (unsigned)W)
+      v = *reinterpret_cast<const uint4*>(xp + (int64_t)((img * H + sy) * W + sx) * x_stride);
+    return v;
   };
-  const int64_t t_beg = (int64_t)blockIdx.x * tiles_per_wg;
-  const int64_t t_end = min(ntiles, t_beg + tiles_per_wg);
-  if (t_beg < t_end) fetch(t_beg);
-  for (int64_t tile = t_beg; tile < t_end; ++tile) {
-    __syncthreads();   // the previous tile's fragments have been read
+  // its place when the first of the rows is in ring slot s (< 2 RING - rows)
+  auto x_place = [&](int p, int s) {
+    const int i = p / WG_XW, c = p - i * WG_XW;
+    int at = s + i;
+    if (at >= RING) at -= RING;
+    return x_dst + at * WG_XROW + wg_piece(c, xc & 3);
+  };
+  uint4 rz[ZIT], rm[ZIT], rx[XIT];
+  auto fetch = [&]() {   // the step's dz rows r0 .. and input rows r0 + 1 ..
 #pragma unroll
     for (int u = 0; u < ZIT; ++u) {
-      const int i = t + 256 * u;
-      const int cg = i >> 6, p = 2 * (i & 63);
-      const uint4 v0 = masked ? apply_mask8(rz[u][0], rm[u][0]) : rz[u][0];
-      const uint4 v1 = masked ? apply_mask8(rz[u][1], rm[u][1]) : rz[u][1];
+      const int p = (t + NT * u) / ZP;
+      const int oy = r0 + p / WG_W, ox = tx0 + p % WG_W;
+      const int64_t pix = (img * H + oy) * W + ox;
+      rz[u] = rm[u] = make_uint4(0, 0, 0, 0);
+      if (z_ok && p < SR * WG_W && oy < H && ox < W) {
+        rz[u] = *reinterpret_cast<const uint4*>(zp + pix * dz.stride);
+        if (mp) rm[u] = *reinterpret_cast<const uint4*>(mp + pix * mask.stride);
+      }
+    }
 #pragma unroll
-      for (int e = 0; e < 8; ++e)
-        *reinterpret_cast<uint32_t*>(&sZ[(8 * cg + e) * WZ_PITCH + p]) = pair_word(v0, v1, e);
+    for (int u = 0; u < XIT; ++u) rx[u] = load_x((t + NT * u) / XP, SR, r0 + 1);
+  };
+  const int dx = wv % 3, rw = (wv / 3) % NR, ciw = (wv / (3 * NR)) % NCI, cow = wv / (3 * NR * NCI);
+  // transposing reads: lane 16 g + i reads 8 bytes of pixel 4 g + i / 4
+  const int px = 4 * (lane >> 4) + ((lane >> 2) & 3), ch = (lane & 3) * 8;
+  const char* a_base[2];
+  const char* b_base[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    a_base[h] = s_z + cow * ZGROUP + rw * 4 * WG_ZROW + wg_piece(px, 2 * h) + ch;
+    b_base[h] = s_x + ciw * XGROUP + wg_piece(px + dx, 2 * h) + ch;
+  }
+  const bool do_bias = dbias != nullptr && ci0 == 0 && ciw == 0 && dx == 1;   // wavefront-uniform
+  f32x4 acc[3][2][2], bacc[2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    bacc[a] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) acc[dy][a][b] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+  const short one = 0x3F80;   // bf16
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, (short8v){one, one, one, one, one, one, one, one});
+
+  locate(k_beg);
+  fetch();
+  int first = 0;   // ring slot of input row r0 - 1
+  bool start = true;   // the first step of the run or of a strip
+  for (int k = k_beg, zbuf = 0; k < k_end; ++k, zbuf ^= 1) {
+    if (start) {   // rows r0 - 1 and r0 as well
+      __syncthreads();   // the previous strip's fragments have been read
+#pragma unroll
+      for (int u = 0; u < HIT; ++u) {
+        const int p = (t + NT * u) / XP;
+        const uint4 v = load_x(p, 2, r0 - 1);
+        if (p < 2 * WG_XW) *reinterpret_cast<uint4*>(x_place(p, first)) = v;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < ZIT; ++u) {
+      const int p = (t + NT * u) / ZP;
+      uint4 v = rz[u];
+      if (mp) {
+        const uint4 m = rm[u];
+        v = make_uint4(mask_word(v.x, m.x), mask_word(v.y, m.y), mask_word(v.z, m.z), mask_word(v.w, m.w));
+      }
+      if (p < SR * WG_W)
+        *reinterpret_cast<uint4*>(z_dst + (zbuf * SR + p / WG_W) * WG_ZROW + wg_piece(p % WG_W, zc & 3)) = v;
     }
 #pragma unroll
     for (int u = 0; u < XIT; ++u) {
-      const int i = t + 256 * u;
-      if (i >= XI) continue;
-      const int cg = i / (WX_H * XROW), pr = i % (WX_H * XROW);
-      const int py = pr / XROW, px = 2 * (pr % XROW);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const uint32_t wd = pair_word(rx[u][0], rx[u][1], e);
-        uint16_t* row0 = &sX[(0 * 32 + 8 * cg + e) * WX_PITCH + py * WT_W];
-        uint16_t* row1 = &sX[(1 * 32 + 8 * cg + e) * WX_PITCH + py * WT_W];
-        uint16_t* row2 = &sX[(2 * 32 + 8 * cg + e) * WX_PITCH + py * WT_W];
-        // copy dx holds patch column c + dx at column c: the pair (px, px + 1)
-        // lands at columns px, px + 1 (dx 0), px - 2, px - 1 (dx 2) as one
-        // word, and at px - 1, px (dx 1) as two halves
-        if (px + 1 < WT_W) *reinterpret_cast<uint32_t*>(row0 + px) = wd;
-        if (px >= 2) *reinterpret_cast<uint32_t*>(row2 + px - 2) = wd;
-        if (px >= 1) row1[px - 1] = (uint16_t)wd;
-        if (px < WT_W) row1[px] = (uint16_t)(wd >> 16);
-      }
+      const int p = (t + NT * u) / XP;
+      if (p < SR * WG_XW) *reinterpret_cast<uint4*>(x_place(p, first + 2)) = rx[u];
     }
     __syncthreads();
-    if (tile + 1 < t_end) fetch(tile + 1);
-    if (do_bias && t < COB) {   // the row of dz^T of channel t (zero outside the image)
-#pragma unroll 4
-      for (int k = 0; k < WT_PX; k += 8) {
-        const uint4 v = *reinterpret_cast<const uint4*>(&sZ[t * WZ_PITCH + k]);
-        const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
+    if (k + 1 < k_end) {
+      locate(k + 1);
+      start = r0 == 0;
+      fetch();
+    }
+    // input row j of the wavefront's six meets dz row j - dy in tap (dy, dx)
+    bf16x8 a[3][2];
+    const int a_off = zbuf * SR * WG_ZROW;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) bacc += bf2f((uint16_t)(w4[e >> 1] >> (16 * (e & 1))));
+    for (int j = 0; j < 6; ++j) {
+      if (j < 4) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) a[j % 3][h] = wg_fragment(a_base[h] + a_off + j * WG_ZROW);
+      }
+      int at = first + 4 * rw + j;
+      if (at >= RING) at -= RING;
+      bf16x8 b[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) b[h] = wg_fragment(b_base[h] + at * WG_XROW);
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) {
+        const int i = j - dy;
+        if (i < 0 || i >= 4) continue;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            acc[dy][h][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i % 3][h], b[q], acc[dy][h][q], 0, 0, 0);
       }
     }
+    if (do_bias) {   // apart, so that the loop above stays one block for the scheduler
 #pragma unroll
-    for (int ks = 0; ks < WT_PX / 32; ++ks) {
-      // this lane's 8 pixels of the K step: tile row r, columns c0 .. c0 + 7
-      const int p = 32 * ks + 8 * (lane >> 4);
-      const int r = p / WT_W, c0 = p % WT_W;
-      bf16x8 a[NCO];
+      for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int c = 0; c < NCO; ++c)
-        a[c] = *reinterpret_cast<const bf16x8*>(
-            &sZ[((co_blk + 2 * c) * 16 + (lane & 15)) * WZ_PITCH + p]);
+        for (int h = 0; h < 2; ++h)
+          bacc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              wg_fragment(a_base[h] + a_off + j * WG_ZROW), ones, bacc[h], 0, 0, 0);
+    }
+    first += SR;
+    if (first >= RING) first -= RING;
+  }
+  // acc[dy][h][q][r]: output channel 16 h + 4 (lane / 16) + r, input channel 16 q +
+  // lane % 16.  The odd 16-lane rows of q = 0 change places with the even ones of
+  // q = 1, so that an atomic instruction covers 32 input channels (a whole
+  // 128-byte line) of two output channels instead of 16 of four.
+  const int co = co0 + 32 * cow, ci = ci0 + 32 * ciw + (lane & 31);
+  const int rows = cout - co - 8 * (lane >> 5);   // valid channels from this lane's first
+  float* d0 = dw + ((int64_t)dx * cout + co + 8 * (lane >> 5)) * cin + ci;
+  auto add = [&](int dy, int h, int r) {
+    const auto sw = __builtin_amdgcn_permlane16_swap(   // by all lanes
+        __float_as_uint(acc[dy][h][0][r]), __float_as_uint(acc[dy][h][1][r]), false, false);
 #pragma unroll
-      for (int u = 0; u < 9; ++u) {
-        const int dy = u / 3, dx = u % 3;
-        const bf16x8 b = *reinterpret_cast<const bf16x8*>(
-            &sX[(dx * 32 + ci_sub * 16 + (lane & 15)) * WX_PITCH + (r + dy) * WT_W + c0]);
+    for (int e = 0; e < 2; ++e) {
+      const int c = 16 * h + 4 * e + r;   // and 8 (lane / 32)
+      if (c < rows && ci < cin)
+        unsafeAtomicAdd(d0 + ((int64_t)3 * dy * cout + c) * cin, __uint_as_float(sw[e]));
+    }
+  };
+  // the wavefronts that shared the rows of a step meet in LDS first: the adds to dw
+  // go through at about one element per clock and memory channel
+  if constexpr (NR > 1) {
+    static_assert(NCO == 1 && NCI == 1 && 3 * 48 * 64 * 4 <= XGROUP, "the partial sums fit the ring");
+    float* s_sum = reinterpret_cast<float*>(s_x) + dx * 48 * 64 + lane;
+    for (int k = 1; k < NR; ++k) {
+      __syncthreads();   // fragments, or the previous sums, have been read
 #pragma unroll
-        for (int c = 0; c < NCO; ++c)
-          acc[c][u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c], b, acc[c][u], 0, 0, 0);
-      }
+      for (int e = 0; e < 48; ++e)
+        if (rw == k) s_sum[e * 64] = acc[e / 16][(e >> 3) & 1][(e >> 2) & 1][e & 3];
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 48; ++e)
+        if (rw == 0) acc[e / 16][(e >> 3) & 1][(e >> 2) & 1][e & 3] += s_sum[e * 64];
     }
   }
-  // dW[tap][co][ci]: acc[c][u][r] is output channel (co_blk + 2 c) 16 +
-  // 4 (lane / 16) + r, input channel ci_sub 16 + lane % 16
+  if (rw == 0) {
 #pragma unroll
-  for (int c = 0; c < NCO; ++c)
+    for (int k = 0; k < 24; ++k) add(k / 8, (k >> 2) & 1, k & 3);
+  }
+  if (do_bias && (lane & 15) == 0) {   // every column holds the row's sum
 #pragma unroll
-    for (int u = 0; u < 9; ++u) {
-      const int ci = ci0 + ci_sub * 16 + (lane & 15);
-      if (ci >= cin) continue;
-      for (int r = 0; r < 4; ++r) {
-        const int co = co0 + (co_blk + 2 * c) * 16 + 4 * (lane >> 4) + r;
-        if (co < cout) unsafeAtomicAdd(&dw[((int64_t)u * cout + co) * cin + ci], acc[c][u][r]);
-      }
-    }
-  if (do_bias && t < COB && co0 + t < cout) unsafeAtomicAdd(&dbias[co0 + t], bacc);
+    for (int h = 0; h < 2; ++h)
+      for (int r = 0; r < 4; ++r)
+        if (co + 16 * h + 4 * (lane >> 4) + r < cout)
+          unsafeAtomicAdd(dbias + co + 16 * h + 4 * (lane >> 4) + r, bacc[h][r]);
+  }
 }
 
 // Narrow weight gradient (cout <= 32): a 32 x 32 channel tile for one row
@@ -1351,19 +1462,29 @@ hipError_t nn_conv3x3_wgrad(const gs_act* x1, const gs_act* x2, const gs_act* dz
   const int cin = x1->c + (x2 ? x2->c : 0);
   const int cout = dz->c;
   const int64_t npix = (int64_t)x1->n * x1->h * x1->w;
-  if (cout <= 32 && cin % 8 == 0 && x1->c % 8 == 0 && cout % 8 == 0) {
-    // narrow layers (the full-resolution ones): spatial tiles; for wider
-    // layers the 64 x 64 channel tiles below measured faster (their MFMA
-    // work per staged byte is larger, and the tile kernel at 64 output
-    // channels holds two workgroups per CU)
-    const int64_t ntiles = (int64_t)x1->n * ((x1->h + WT_H - 1) / WT_H) * ((x1->w + WT_W - 1) / WT_W);
-    const int64_t blocks_ch = (cin + 31) / 32;
-    // runs of tiles: about 1,024 workgroups, each long enough that its
-    // 9 x 32 x 32 closing atomics are few next to its MFMA work
-    const int64_t per = std::max<int64_t>(4, (ntiles * blocks_ch + 1023) / 1024);
-    const dim3 grid((unsigned)((ntiles + per - 1) / per), 1u, (unsigned)blocks_ch);
-    hipLaunchKernelGGL(conv3x3_wgrad_patch_kernel<32>, grid, dim3(256), 0, s, view(x1), view(x2),
-                       view(dz), view(mask), x1->n, x1->h, x1->w, cout, cin, (int)per, dw, dbias);
+  if (cin % 8 == 0 && x1->c % 8 == 0 && cout % 8 == 0) {
+    // 32 output channels per workgroup up to 32, else 64; 32 input channels for
+    // an odd number of 32-channel groups, else 64 (with 64 output channels)
+    const bool one_co = cout <= 32, one_ci = one_co || (cin + 31) / 32 % 2 == 1;
+    const int rows = one_co ? 8 : 4;   // per step
+    const int steps = x1->n * ((x1->w + WG_W - 1) / WG_W) * ((x1->h + rows - 1) / rows);
+    const int ci_groups = one_ci ? (cin + 31) / 32 : (cin + 63) / 64;
+    const int pairs = ci_groups * (one_co ? (cout + 31) / 32 : (cout + 63) / 64);
+    // as many runs of steps as there are workgroups that the CUs hold: each ends
+    // with an atomic add per weight (twice as many runs, 9 and 19 million adds
+    // instead of 5 and 9, cost 20-30 us more; half as many leave CUs idle)
+    const int runs_wanted = std::max(1, (one_ci ? 512 : 256) / pairs);
+    const int per = (steps + runs_wanted - 1) / runs_wanted;
+    const int runs = (steps + per - 1) / per;
+    const unsigned grid = (unsigned)((runs + 7) / 8 * 8 * pairs);
+#define GS_WGRAD(O, I, R)                                                                       \
+  hipLaunchKernelGGL((conv3x3_wgrad_strip_kernel<O, I, R>), dim3(grid), dim3(64 * 3 * O * I * R), 0, \
+                     s, view(x1), view(x2), view(dz), view(mask), x1->n, x1->h, x1->w, cout, cin, \
+                     pairs, ci_groups, per, dw, dbias)
+    if (one_co) GS_WGRAD(1, 1, 2);
+    else if (one_ci) GS_WGRAD(2, 1, 1);
+    else GS_WGRAD(2, 2, 1);
+#undef GS_WGRAD
     return hipGetLastError();
   }
   // pixel chunks: enough workgroups to fill the chip, each long enough that

@@ -20,6 +20,8 @@
 // MFMA 16x16x32 operand layout (lane l, 8 values each): A row l % 16, B
 // column l % 16, both covering k = 8 (l / 16) .. 8 (l / 16) + 7; result D row
 // 4 (l / 16) + j, column l % 16, j = 0..3.
+#include <cmath>
+
 #include "gs_internal.h"
 #include "gs_nn.h"
 
@@ -544,9 +546,9 @@ __global__ __launch_bounds__(256) void conv3x3_wgrad_kernel(
 // about the same LDS reads per MFMA, since an input row's fragments serve the
 // three taps of the column against three rows of dz held in registers.
 //
-// 4 x 640x480, 96 -> 32 channels: 147 us (402 MB needed, 85 at this card's copy
+// 4 x 640x480, 96 -> 32 channels: 139 us (402 MB needed, 85 at this card's copy
 // rate), 276 on 16 x 8 tiles transposed by the VALU with three shifted copies of
-// the input. 8 x 160x120, 128 -> 128: 88 us, 31 of them the closing adds, 160
+// the input. 8 x 160x120, 128 -> 128: 81 us, 31 of them the closing adds, 147
 // with a row of taps per workgroup. What is left is issue and LDS latency at three
 // wavefronts per SIMD: without the loads 128 and 84 us, without the MFMAs 152 and
 // 78 (before the row halves met in LDS, which took 10 us off the first).
@@ -599,15 +601,17 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
   __shared__ __attribute__((aligned(16))) char s_x[NCI * XGROUP];
   const int t = threadIdx.x, lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
-  // all channel pairs of a run of steps on one XCD (workgroups go round the eight
-  // of them), close in time: what they share comes from its L2
-  const int slot = (int)blockIdx.x >> 3;
-  const int run = (slot / n_pairs) * 8 + ((int)blockIdx.x & 7), pair = slot % n_pairs;
+  // an eighth of the (run of steps, channel pair) list to each XCD (workgroups go
+  // round the eight of them): the pairs of a run, but for those at an eighth's end,
+  // share what they read in its L2
+  const int item = ((int)blockIdx.x & 7) * (int)(gridDim.x >> 3) + ((int)blockIdx.x >> 3);
+  const int run = item / n_pairs, pair = item % n_pairs;
   const int co0 = (pair / ci_groups) * 32 * NCO, ci0 = (pair % ci_groups) * 32 * NCI;
   const int strips = (W + WG_W - 1) / WG_W, strip_steps = (H + SR - 1) / SR;
   const int n_steps = N * strips * strip_steps;
-  const int k_beg = run * steps_per_wg, k_end = min(n_steps, k_beg + steps_per_wg);
-  if (k_beg >= k_end) return;   // the whole workgroup
+  const int64_t k_beg64 = (int64_t)run * steps_per_wg;
+  if (k_beg64 >= n_steps) return;   // the whole workgroup
+  const int k_beg = (int)k_beg64, k_end = min(n_steps, k_beg + steps_per_wg);
 
   // this thread's pieces: channels 8 zc .. of dz (and mask), 8 xc .. of the input
   const int zc = t % ZP, xc = t % XP;
@@ -621,18 +625,20 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
   char* z_dst = s_z + (zc >> 2) * ZGROUP;
   char* x_dst = s_x + (xc >> 2) * XGROUP;
   int img = 0, tx0 = 0, r0 = 0;   // of the step: image, first column, first row
+  int64_t base = 0;               // of the image: its first pixel
   auto locate = [&](int k) {
     const int strip = k / strip_steps;
     img = strip / strips;
     tx0 = (strip - img * strips) * WG_W;
     r0 = (k - strip * strip_steps) * SR;
+    base = (int64_t)img * H * W;
   };
   // piece p of 34-pixel input rows from row r on (rows of the image only)
   auto load_x = [&](int p, int rows, int r) {
     const int i = p / WG_XW, sy = r + i, sx = tx0 + (p - i * WG_XW) - 1;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (x_ok && i < rows && (unsigned)sy < (unsigned)H && (unsigned)sx < (unsigned)W)
-      v = *reinterpret_cast<const uint4*>(xp + (int64_t)((img * H + sy) * W + sx) * x_stride);
+      v = *reinterpret_cast<const uint4*>(xp + (base + sy * W + sx) * x_stride);
     return v;
   };
   // its place when the first of the rows is in ring slot s (< 2 RING - rows)
@@ -648,7 +654,7 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
     for (int u = 0; u < ZIT; ++u) {
       const int p = (t + NT * u) / ZP;
       const int oy = r0 + p / WG_W, ox = tx0 + p % WG_W;
-      const int64_t pix = (img * H + oy) * W + ox;
+      const int64_t pix = base + oy * W + ox;
       rz[u] = rm[u] = make_uint4(0, 0, 0, 0);
       if (z_ok && p < SR * WG_W && oy < H && ox < W) {
         rz[u] = *reinterpret_cast<const uint4*>(zp + pix * dz.stride);
@@ -699,10 +705,7 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
     for (int u = 0; u < ZIT; ++u) {
       const int p = (t + NT * u) / ZP;
       uint4 v = rz[u];
-      if (mp) {
-        const uint4 m = rm[u];
-        v = make_uint4(mask_word(v.x, m.x), mask_word(v.y, m.y), mask_word(v.z, m.z), mask_word(v.w, m.w));
-      }
+      if (mp) v = apply_mask8(v, rm[u]);
       if (p < SR * WG_W)
         *reinterpret_cast<uint4*>(z_dst + (zbuf * SR + p / WG_W) * WG_ZROW + wg_piece(p % WG_W, zc & 3)) = v;
     }
@@ -1462,7 +1465,8 @@ hipError_t nn_conv3x3_wgrad(const gs_act* x1, const gs_act* x2, const gs_act* dz
   const int cin = x1->c + (x2 ? x2->c : 0);
   const int cout = dz->c;
   const int64_t npix = (int64_t)x1->n * x1->h * x1->w;
-  if (cin % 8 == 0 && x1->c % 8 == 0 && cout % 8 == 0) {
+  if (cin % 8 == 0 && x1->c % 8 == 0 && cout % 8 == 0 &&
+      (int64_t)x1->h * x1->w < (int64_t)1 << 31) {   // pixels of an image: 32-bit numbers there
     // 32 output channels per workgroup up to 32, else 64; 32 input channels for
     // an odd number of 32-channel groups, else 64 (with 64 output channels)
     const bool one_co = cout <= 32, one_ci = one_co || (cin + 31) / 32 % 2 == 1;
@@ -1470,13 +1474,20 @@ hipError_t nn_conv3x3_wgrad(const gs_act* x1, const gs_act* x2, const gs_act* dz
     const int steps = x1->n * ((x1->w + WG_W - 1) / WG_W) * ((x1->h + rows - 1) / rows);
     const int ci_groups = one_ci ? (cin + 31) / 32 : (cin + 63) / 64;
     const int pairs = ci_groups * (one_co ? (cout + 31) / 32 : (cout + 63) / 64);
-    // as many runs of steps as there are workgroups that the CUs hold: each ends
-    // with an atomic add per weight (twice as many runs, 9 and 19 million adds
-    // instead of 5 and 9, cost 20-30 us more; half as many leave CUs idle)
-    const int runs_wanted = std::max(1, (one_ci ? 512 : 256) / pairs);
+    // B workgroups share the steps S pairs, about 3 us each, and every one closes with
+    // 9,216 adds per 32 x 32 channel pair of its `own`, which the memory channels that
+    // hold dw (36 KB per pair) take at some 60 per ns and pair, 200 in all: the sum of
+    // both is least at B^2 = S pairs / own by 16 per pair of dw, at most 50.  From one
+    // to one per CU: a second on some CUs makes these the last (8 x 160x120, 96 -> 32:
+    // 45 us with 424 workgroups, 32 with 256), one on each costs as much in adds as it
+    // hides (4 x 640x480, 32 -> 32: 94 and 72 us).
+    const int own = one_co ? 1 : one_ci ? 2 : 4;
+    const double ratio = std::min(50.0, 16.0 * own * pairs);
+    const int blocks = std::min(256, (int)std::sqrt(ratio * steps * pairs / own));
+    const int runs_wanted = std::max(1, blocks / pairs);
     const int per = (steps + runs_wanted - 1) / runs_wanted;
     const int runs = (steps + per - 1) / per;
-    const unsigned grid = (unsigned)((runs + 7) / 8 * 8 * pairs);
+    const unsigned grid = (unsigned)((runs * (int64_t)pairs + 7) / 8 * 8);
 #define GS_WGRAD(O, I, R)                                                                       \
   hipLaunchKernelGGL((conv3x3_wgrad_strip_kernel<O, I, R>), dim3(grid), dim3(64 * 3 * O * I * R), 0, \
                      s, view(x1), view(x2), view(dz), view(mask), x1->n, x1->h, x1->w, cout, cin, \

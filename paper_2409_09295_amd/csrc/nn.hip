@@ -1,21 +1,24 @@
 // Kernels of the learned Gaussian initialiser: a small U-Net over BF16 NHWC
 // activations with FP32 accumulation on MFMA (v_mfma_f32_16x16x32_bf16).
 //
-// conv3x3 (forward and, with flipped/transposed weights, backward-data) is an
-// implicit GEMM: M = pixels, N = output channels, K = 9 taps x input
-// channels.  A 256-thread workgroup owns a 64-pixel x 64-channel tile; each
-// wavefront computes a 32 x 32 quarter as 2 x 2 MFMA tiles.  Per K step
-// (one tap, 32 input channels) the workgroup stages the 64 x 32 activation
-// slice (zero outside the image; channels may come from two tensors, which
-// is how the decoder's skip concatenation is read without materialising it)
-// and the 64 x 32 weight slice in LDS, both K-contiguous so that every MFMA
-// operand fragment is one 16-byte LDS read.  An optional mask tensor zeroes
-// input entries whose mask value is <= 0 (the ReLU backward fused into the
+// conv3x3 (forward and, with flipped/transposed weights, backward-data) runs as
+// conv3x3_patch_kernel, a direct convolution on spatial tiles, where channels come
+// in eights.  Other channel counts run as an implicit GEMM, conv3x3_kernel: M =
+// pixels, N = output channels, K = 9 taps x input channels.  A 256-thread workgroup
+// owns a 64-pixel x 64-channel tile; each wavefront computes a 32 x 32 quarter as
+// 2 x 2 MFMA tiles.  Per K step (one tap, 32 input channels) the workgroup stages
+// the 64 x 32 activation slice (zero outside the image; channels may come from two
+// tensors, which is how the decoder's skip concatenation is read without
+// materialising it) and the 64 x 32 weight slice in LDS, both K-contiguous so that
+// every MFMA operand fragment is one 16-byte LDS read.  An optional mask tensor
+// zeroes input entries whose mask value is <= 0 (the ReLU backward fused into the
 // backward-data pass).
 //
 // conv3x3_wgrad: dW[tap][co][ci] = sum_p dz[p][co] x[p + tap][ci] as a GEMM
-// with M = Cout, N = Cin, K = pixels, split over pixel chunks with float32
-// atomics; tiles are transposed through LDS so fragments stay contiguous.
+// with M = Cout, N = Cin, K = pixels, split over runs of pixels with float32
+// atomics: conv3x3_wgrad_strip_kernel for channels in eights, which reads the
+// tiles transposed from LDS; conv3x3_wgrad_kernel and conv3x3_wgrad32_kernel for
+// the others, which write them transposed.
 //
 // MFMA 16x16x32 operand layout (lane l, 8 values each): A row l % 16, B
 // column l % 16, both covering k = 8 (l / 16) .. 8 (l / 16) + 7; result D row
@@ -41,6 +44,13 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)(r >> 16);
 }
 
+// Two floats as bf16 in one word, rounded as f2bf rounds.
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  typedef float float2v __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){lo, hi}, bf16x2));
+}
+
 constexpr int BM = 64, BN = 64, BK = 32;
 constexpr int LDK = BK + 8;   // LDS row pitch in bf16 (16-byte aligned, skews banks)
 
@@ -49,16 +59,17 @@ struct ActView {
   int32_t c, stride, offset;
 };
 
-// Zeroes the bf16 elements of v whose mask element is <= 0.
+// Zeroes the bf16 elements of v whose mask element is <= 0 (as int16, -0 among
+// them: 0 - x saturates, so its sign is set exactly where x > 0).
+__device__ __forceinline__ uint32_t mask_word(uint32_t v, uint32_t mk) {
+  typedef short short2v __attribute__((ext_vector_type(2)));
+  const short2v m = __builtin_elementwise_sub_sat(short2v{0, 0}, __builtin_bit_cast(short2v, mk));
+  return v & __builtin_bit_cast(uint32_t, (short2v)(m >> (short)15));
+}
+
 __device__ __forceinline__ uint4 apply_mask8(uint4 v, uint4 mk) {
-  const uint32_t mw[4] = {mk.x, mk.y, mk.z, mk.w};
-  uint32_t vw[4] = {v.x, v.y, v.z, v.w};
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t lo = (int16_t)(mw[q] & 0xFFFF) > 0 ? 0xFFFFu : 0u;   // bf16 > 0 <=> int16 > 0
-    const uint32_t hi = (int16_t)(mw[q] >> 16) > 0 ? 0xFFFF0000u : 0u;
-    vw[q] &= (lo | hi);
-  }
-  return make_uint4(vw[0], vw[1], vw[2], vw[3]);
+  return make_uint4(mask_word(v.x, mk.x), mask_word(v.y, mk.y), mask_word(v.z, mk.z),
+                    mask_word(v.w, mk.w));
 }
 
 // Loads 8 consecutive channels [c0, c0 + 8) of pixel (n, y, x) from a
@@ -195,176 +206,221 @@ __global__ __launch_bounds__(256) void conv3x3_kernel(
 }
 
 // Direct 3x3 convolution on spatial tiles.  A workgroup computes 16 x 16
-// pixel tiles of one image for BNT output channels; wavefront w computes
-// output rows 4w .. 4w + 3 (each a 16-pixel MFMA row block) for all BNT
-// channels.  Input channels go in chunks of 32: the chunk's 18 x 18 input
-// patch (the tile and its one-pixel halo; zero outside the image) and its
-// 9 x BNT x 32 weights are staged in LDS once, and every tap's A fragments
-// are read from the patch at the tap's offset, so each input value is loaded
-// from memory about 1.3 times instead of nine.  Workgroups are persistent:
-// workgroup b takes tiles b, b + gridDim.x, ..., and the next (tile, chunk)
-// pair's patch and weights are loaded into registers while this pair's
-// 9 x 4 x BNT/16 MFMAs per wavefront run, so a layer with a single chunk
-// overlaps the next tile's loads with this tile's products and stores.  With
-// a single chunk the weights stay in LDS for all of a workgroup's tiles.
+// pixel tiles of one image for 16 JN output channels; wavefront w of eight
+// computes output rows 2w and 2w + 1 for all of them (four rows in four
+// wavefronts read fewer fragments but held two or three wavefronts per SIMD).  Input channels go in chunks of 32:
+// the chunk's 18 x 18 input patch (the tile and its one-pixel halo; zero outside
+// the image) and its 9 x 16 JN x 32 weights are staged in LDS once, and every
+// tap reads the patch at its offset, so each input value is loaded from memory
+// about 1.3 times instead of nine.  Workgroups are persistent: those of
+// column c take tiles c, c + columns, ..., and the next (tile, chunk) pair's patch and
+// weights are loaded into registers while this pair's 18 JN MFMAs per wavefront
+// run, so a layer with a single chunk overlaps the next tile's loads with this
+// tile's products and stores.
+//
+// The weights are the A operand and 16 pixels of a row the B operand, so a lane
+// ends with 4 JN consecutive channels of one pixel (A row 4 g + r of block j holds
+// channel 4 JN g + 4 j + r) and stores them 16 bytes at a time; four patch rows
+// per tap column serve its three taps.  LDS pixels and weight rows are 64 bytes,
+// their four 16-byte pieces permuted by a function of the pixel's column (the
+// weight's row) that leaves the 16 lanes of an LDS read cycle, {0-3, 12-15, 20-27}
+// and so on, on different banks.
+//
+// 4 x 640x480, forward: 32 -> 32 channels 33 us (65 with pixels as the A operand, a
+// 16-channel span per lane group and 2-byte stores), 96 -> 32 100 (133), 64 -> 64 121
+// (197); with a mask, 96 of 32 channels 139 (232), 32 of 64 109 (131).  157 MB and 315 MB
+// of activations would take 33 and 66 us at the 4.7 TB/s of a copy: one chunk is bound
+// by memory, several by the LDS reads of the fragments (eight bytes per pixel and
+// channel block for 2 x 16 x 32 products) and the two barriers of a chunk.
 constexpr int PT = 16;                  // output tile side
 constexpr int PP = PT + 2;              // patch side (with halo)
 constexpr int PCC = 32;                 // input channels per chunk
-constexpr int PPITCH = PCC + 8;         // LDS pitch in bf16 (80 bytes: 16-byte rows, spread banks)
+constexpr int PPITCH = 20;              // LDS pixels per patch row
+constexpr int PR = 2;                   // output rows per wavefront
 constexpr int PATCH_CHUNKS = PP * PP * (PCC / 8);   // 16-byte pieces of a patch (1,296)
 
+// Byte offset of 16-byte piece c of the 64-byte record i of a row of records.
+__device__ __forceinline__ int cv_piece(int i, int c) {
+  return i * 64 + ((c ^ (-(i >> 2) & 3)) << 4);
+}
+
 // MASKED: the input is multiplied by a ReLU mask (mask > 0) as it is staged.
-template <int BNT, bool MASKED>
-__global__ __launch_bounds__(256, BNT == 32 ? 3 : 2) void conv3x3_patch_kernel(
+// ONE: a single chunk (cin <= 32), whose weights stay in LDS.
+template <int JN, bool MASKED, bool ONE>
+__global__ __launch_bounds__(64 * PT / PR, 4) void conv3x3_patch_kernel(
     ActView x1, ActView x2, ActView mask, int N, int H, int W, const uint16_t* __restrict__ wk,
     int cout, int cin, const float* __restrict__ bias, int relu, uint16_t* __restrict__ y,
-    int y_stride, int y_offset, float* __restrict__ yf, int yf_stride) {
-  constexpr int JN = BNT / 16;
+    int y_stride, int y_offset, float* __restrict__ yf, int yf_stride, int columns) {
+  constexpr int BNT = 16 * JN;
+  constexpr int NT = 64 * PT / PR;                  // threads
   constexpr int W_CHUNKS = 9 * BNT * (PCC / 8);     // 16-byte pieces of a chunk's weights
-  constexpr int PA = (PATCH_CHUNKS + 255) / 256;    // per thread
-  constexpr int PB = (W_CHUNKS + 255) / 256;
-  __shared__ __attribute__((aligned(16))) uint16_t sP[PP * PP * PPITCH];
-  __shared__ __attribute__((aligned(16))) uint16_t sW[9 * BNT * PPITCH];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  constexpr int PA = (PATCH_CHUNKS + NT - 1) / NT;    // per thread
+  constexpr int PB = (W_CHUNKS + NT - 1) / NT;
+  __shared__ __attribute__((aligned(16))) char sP[PP * PPITCH * 64];
+  __shared__ __attribute__((aligned(16))) char sW[9 * BNT * 64];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int tiles_x = (W + PT - 1) / PT, tiles_y = (H + PT - 1) / PT;
   const int n_tiles = N * tiles_x * tiles_y;
-  const int n0 = blockIdx.y * BNT;
-  const int nchunks = (cin + PCC - 1) / PCC;
-  const bool w_resident = nchunks == 1;   // the weights are loaded once per workgroup
-  const ActView none = {nullptr, 0, 0, 0};
+  // the channel groups of a column of tiles on one XCD (workgroups go round the eight
+  // of them), close in time: they read it through one L2
+  const int groups = (cout + BNT - 1) / BNT, slot = (int)blockIdx.x >> 3;
+  const int column = slot / groups * 8 + ((int)blockIdx.x & 7), n0 = slot % groups * BNT;
+  if (column >= columns) return;   // the whole workgroup
+  const int nchunks = ONE ? 1 : (cin + PCC - 1) / PCC;
+  // this thread's pieces hold channels pc .. pc + 7 of a chunk
+  const int pc = (t & 3) * 8;
   uint4 ra[PA], rm[MASKED ? PA : 1], rb[PB];
-  auto fetch = [&](int tile, int chunk, bool weights) {
-    const int img = tile / (tiles_x * tiles_y);
+  int img = 0, ty0 = 0, tx0 = 0;   // of the tile last located
+  auto locate = [&](int tile) {
+    img = tile / (tiles_x * tiles_y);
     const int trem = tile - img * tiles_x * tiles_y;
-    const int ty0 = (trem / tiles_x) * PT, tx0 = (trem % tiles_x) * PT;
-    const int c0 = chunk * PCC;
+    ty0 = (trem / tiles_x) * PT;
+    tx0 = (trem % tiles_x) * PT;
+  };
+  auto fetch = [&](int chunk, bool weights) {   // of the tile last located
+    const int c = chunk * PCC + pc;
+    const bool first = c < x1.c;
+    const ActView& s = first ? x1 : x2;
+    const int64_t base = (int64_t)img * H * W;
+    const uint16_t* src = s.p + s.offset + (first ? c : c - x1.c) + base * s.stride;
+    const uint16_t* msrc = MASKED ? mask.p + mask.offset + c + base * mask.stride : nullptr;
 #pragma unroll
     for (int u = 0; u < PA; ++u) {
-      const int q = t + 256 * u;            // piece q: patch pixel q / 4, channels 8 (q % 4)
-      const int pp = q >> 2, cc = (q & 3) * 8;
-      const int py = pp / PP, px = pp - py * PP;
-      const int sy = ty0 + py - 1, sx = tx0 + px - 1;
-      const bool inb = q < PATCH_CHUNKS && sy >= 0 && sy < H && sx >= 0 && sx < W &&
-                       c0 + cc < cin;
-      const int64_t pix = ((int64_t)img * H + sy) * W + sx;
-      ra[u] = load8(x1, x2, none, pix, inb, c0 + cc);
-      if constexpr (MASKED) rm[u] = load8(mask, none, none, pix, inb, c0 + cc);
+      const int pp = (t + NT * u) >> 2;    // patch pixel
+      const int py = pp / PP, sy = ty0 + py - 1, sx = tx0 + (pp - py * PP) - 1;
+      ra[u] = make_uint4(0, 0, 0, 0);
+      if constexpr (MASKED) rm[u] = ra[u];
+      if (pp < PP * PP && (unsigned)sy < (unsigned)H && (unsigned)sx < (unsigned)W && c < cin) {
+        const int64_t pix = sy * W + sx;
+        ra[u] = *reinterpret_cast<const uint4*>(src + pix * s.stride);
+        if constexpr (MASKED) rm[u] = *reinterpret_cast<const uint4*>(msrc + pix * mask.stride);
+      }
     }
     if (!weights) return;
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
-      const int q = t + 256 * u;            // piece q: (tap, channel n) = q / 4, inputs 8 (q % 4)
-      const int tn = q >> 2, cc = (q & 3) * 8;
-      const int tap = tn / BNT, co = n0 + (tn - tap * BNT);
+      const int tn = (t + NT * u) >> 2;    // (tap, LDS row): row 16 j + 4 g + r of a tap
+      const int tap = tn / BNT, row = tn - tap * BNT;
+      const int co = n0 + 4 * JN * ((row >> 2) & 3) + 4 * (row >> 4) + (row & 3);
       rb[u] = make_uint4(0, 0, 0, 0);
-      if (q < W_CHUNKS && co < cout && c0 + cc < cin)
-        rb[u] = *reinterpret_cast<const uint4*>(wk + ((int64_t)tap * cout + co) * cin + c0 + cc);
+      if (tn < 9 * BNT && co < cout && c < cin)
+        rb[u] = *reinterpret_cast<const uint4*>(wk + ((int64_t)tap * cout + co) * cin + c);
     }
   };
-  f32x4 acc[4][JN];
+  f32x4 acc[PR][JN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < PR; ++i)
 #pragma unroll
     for (int j = 0; j < JN; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
   // registers -> LDS: the patch, and the weights when they are (re)loaded
   auto stage = [&](bool weights) {
 #pragma unroll
     for (int u = 0; u < PA; ++u) {
-      const int q = t + 256 * u;
-      if (q < PATCH_CHUNKS) {
-        uint4 v = ra[u];
-        if constexpr (MASKED) v = apply_mask8(v, rm[u]);
-        *reinterpret_cast<uint4*>(&sP[(q >> 2) * PPITCH + (q & 3) * 8]) = v;
-      }
+      const int pp = (t + NT * u) >> 2, py = pp / PP;
+      uint4 v = ra[u];
+      if constexpr (MASKED) v = apply_mask8(v, rm[u]);
+      if (pp < PP * PP)
+        *reinterpret_cast<uint4*>(sP + py * PPITCH * 64 + cv_piece(pp - py * PP, t & 3)) = v;
     }
     if (!weights) return;
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
-      const int q = t + 256 * u;
-      if (q < W_CHUNKS) *reinterpret_cast<uint4*>(&sW[(q >> 2) * PPITCH + (q & 3) * 8]) = rb[u];
+      const int tn = (t + NT * u) >> 2;
+      if (tn < 9 * BNT)
+        *reinterpret_cast<uint4*>(sW + (tn & ~15) * 64 + cv_piece(tn & 15, t & 3)) = rb[u];
     }
   };
+  const char* w_base = sW + cv_piece(lane & 15, lane >> 4);
+  const char* p_base = sP + PR * wv * PPITCH * 64;
   auto multiply = [&]() {
-#pragma unroll 1
-    for (int tap = 0; tap < 9; ++tap) {
-      const int dy = tap / 3, dx = tap % 3;   // patch offsets of the tap (0 .. 2)
-      bf16x8 a[4], b[JN];
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = *reinterpret_cast<const bf16x8*>(
-            &sP[((4 * wv + i + dy) * PP + (lane & 15) + dx) * PPITCH + 8 * (lane >> 4)]);
+    for (int dx = 0; dx < 3; ++dx) {
+      bf16x8 p[PR + 2];
+      const char* pl = p_base + cv_piece((lane & 15) + dx, lane >> 4);
 #pragma unroll
-      for (int j = 0; j < JN; ++j)
-        b[j] = *reinterpret_cast<const bf16x8*>(
-            &sW[(tap * BNT + j * 16 + (lane & 15)) * PPITCH + 8 * (lane >> 4)]);
+      for (int i = 0; i < PR + 2; ++i) p[i] = *reinterpret_cast<const bf16x8*>(pl + i * PPITCH * 64);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int dy = 0; dy < 3; ++dy)
 #pragma unroll
-        for (int j = 0; j < JN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < JN; ++j) {
+          const bf16x8 w = *reinterpret_cast<const bf16x8*>(w_base + ((3 * dy + dx) * BNT + 16 * j) * 64);
+#pragma unroll
+          for (int i = 0; i < PR; ++i)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, p[i + dy], acc[i][j], 0, 0, 0);
+        }
     }
   };
   // bias, ReLU, bf16 (or float32) store, accumulators cleared; acc[i][j][r] is
-  // output row 4 wv + i, column 4 (lane / 16) + r, channel n0 + 16 j + lane % 16
+  // output row PR wv + i, column lane % 16, channel c0 + 4 j + r
+  const int c0 = n0 + 4 * JN * (lane >> 4);
+  const bool wide = cout % 8 == 0 && y_stride % 8 == 0 && y_offset % 8 == 0 &&
+                    (reinterpret_cast<uintptr_t>(y) & 15) == 0;
+  static_assert(JN % 2 == 0, "eight channels to a store");
   auto epilogue = [&](int tile) {
-    const int img = tile / (tiles_x * tiles_y);
-    const int trem = tile - img * tiles_x * tiles_y;
-    const int ty0 = (trem / tiles_x) * PT, tx0 = (trem % tiles_x) * PT;
+    const int timg = tile / (tiles_x * tiles_y);
+    const int trem = tile - timg * tiles_x * tiles_y;
+    const int oy0 = (trem / tiles_x) * PT + PR * wv, ox = (trem % tiles_x) * PT + (lane & 15);
+    const int64_t base = (int64_t)timg * H * W;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int oy = ty0 + 4 * wv + i;
+    for (int j = 0; j < JN; j += 2) {   // channels c0 + 4 j .. + 7
+      float b[8];
 #pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        const int co = n0 + j * 16 + (lane & 15);
-        if (oy < H && co < cout) {
-          const float bco = bias ? bias[co] : 0.f;
-          for (int r = 0; r < 4; ++r) {
-            const int ox = tx0 + 4 * (lane >> 4) + r;
-            if (ox >= W) continue;
-            const int64_t p = ((int64_t)img * H + oy) * W + ox;
-            float v = acc[i][j][r] + bco;
-            if (relu) v = fmaxf(v, 0.f);
-            if (y) y[p * y_stride + y_offset + co] = f2bf(v);
-            if (yf) yf[p * yf_stride + co] = v;
-          }
+      for (int c = 0; c < 8; ++c) b[c] = bias && c0 + 4 * j + c < cout ? bias[c0 + 4 * j + c] : 0.f;
+#pragma unroll
+      for (int i = 0; i < PR; ++i) {
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          v[c] = acc[i][j + (c >> 2)][c & 3] + b[c];
+          if (relu) v[c] = fmaxf(v[c], 0.f);
         }
-        acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        acc[i][j] = acc[i][j + 1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        const int oy = oy0 + i;
+        if (oy >= H || ox >= W) continue;
+        const int64_t p = base + oy * W + ox;
+        uint16_t* o = y + p * y_stride + y_offset + c0 + 4 * j;
+        if (y && wide) {
+          if (c0 + 4 * j < cout)
+            *reinterpret_cast<uint4*>(o) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]),
+                                                      pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
+        } else if (y) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c)
+            if (c0 + 4 * j + c < cout) o[c] = f2bf(v[c]);
+        }
+        if (yf) {
+          float* of = yf + p * yf_stride + c0 + 4 * j;
+#pragma unroll
+          for (int c = 0; c < 8; ++c)
+            if (c0 + 4 * j + c < cout) of[c] = v[c];
+        }
       }
     }
   };
-  int tile = blockIdx.x;
-  if (tile >= n_tiles) return;   // the grid never exceeds the tiles; uniform over the workgroup
-  fetch(tile, 0, true);
-  if constexpr (MASKED) {
-    // one tile per workgroup: the next chunk's loads overlap this chunk's products
-    for (int chunk = 0; chunk < nchunks; ++chunk) {
-      __syncthreads();   // the previous chunk's fragments have been read
-      stage(true);
-      __syncthreads();
-      if (chunk + 1 < nchunks) fetch(tile, chunk + 1, true);
-      multiply();
+  int tile = column, chunk = 0;   // columns never exceed the tiles
+  locate(tile);
+  fetch(0, true);
+  for (bool first = true;; first = false) {
+    __syncthreads();   // the previous pair's fragments have been read
+    stage(first || !ONE);
+    __syncthreads();
+    // the next (tile, chunk) pair, loaded while this one is multiplied
+    int next_tile = tile, next_chunk = chunk + 1;
+    if (next_chunk == nchunks) {
+      next_chunk = 0;
+      next_tile = tile + columns;
     }
-    epilogue(tile);
-  } else {
-    int chunk = 0;
-    for (bool first = true;; first = false) {
-      __syncthreads();   // the previous pair's fragments have been read
-      stage(first || !w_resident);
-      __syncthreads();
-      // the next (tile, chunk) pair, loaded while this one is multiplied
-      int next_tile = tile, next_chunk = chunk + 1;
-      if (next_chunk == nchunks) {
-        next_chunk = 0;
-        next_tile = tile + (int)gridDim.x;
-      }
-      const bool more = next_tile < n_tiles;
-      if (more) fetch(next_tile, next_chunk, !w_resident);
-      multiply();
-      if (chunk == nchunks - 1) epilogue(tile);
-      if (!more) break;
-      tile = next_tile;
-      chunk = next_chunk;
+    const bool more = next_tile < n_tiles;
+    if (more) {
+      if (next_tile != tile) locate(next_tile);
+      fetch(next_chunk, !ONE);
     }
+    multiply();
+    if (chunk == nchunks - 1) epilogue(tile);
+    if (!more) break;
+    tile = next_tile;
+    chunk = next_chunk;
   }
 }
 
@@ -563,14 +619,6 @@ typedef short short8v __attribute__((ext_vector_type(8)));
 // Byte offset of 16-byte piece c (of 4) of pixel p of a row in LDS.
 __device__ __forceinline__ int wg_piece(int p, int c) {
   return p * 64 + ((c ^ (((p >> 2) & 1) << 1)) << 4);
-}
-
-// Zeroes the bf16 elements of v whose mask element is <= 0 (as int16, -0 among
-// them: 0 - x saturates, so its sign is set exactly where x > 0).
-__device__ __forceinline__ uint32_t mask_word(uint32_t v, uint32_t mk) {
-  typedef short short2v __attribute__((ext_vector_type(2)));
-  const short2v m = __builtin_elementwise_sub_sat(short2v{0, 0}, __builtin_bit_cast(short2v, mk));
-  return v & __builtin_bit_cast(uint32_t, (short2v)(m >> (short)15));
 }
 
 // Fragment: this lane's channel (of the 16 at the address) at pixels 4 g .. 4 g
@@ -1387,21 +1435,26 @@ ActView view(const gs_act* a) {
 
 unsigned blocks(int64_t n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
-// The unmasked patch convolution is persistent: as many workgroups as the
-// device holds at once (split over the channel tiles), never more than there
-// are tiles.
-template <int BNT, bool MASKED>
+// The patch convolution is persistent: as many workgroups as the device holds at
+// once (split over the channel tiles), never more than there are tiles.
+template <int JN, bool MASKED, bool ONE>
 hipError_t launch_patch(ActView x1, ActView x2, ActView mask, int n, int h, int w,
                         const uint16_t* wp, int cout, int cin, const float* bias, int relu,
                         uint16_t* yp, int ys, int yo, float* yf, int yf_stride, unsigned tiles,
                         hipStream_t s) {
-  const unsigned gy = (unsigned)((cout + BNT - 1) / BNT);
-  const int resident = resident_workgroups((const void*)conv3x3_patch_kernel<BNT, MASKED>, 256);
-  unsigned gx = tiles;   // masked calls: one tile per workgroup
-  if (!MASKED && resident > 0)
-    gx = std::min(tiles, std::max(1u, ((unsigned)resident + gy - 1) / gy));
-  hipLaunchKernelGGL((conv3x3_patch_kernel<BNT, MASKED>), dim3(gx, gy), dim3(256), 0, s, x1, x2,
-                     mask, n, h, w, wp, cout, cin, bias, relu, yp, ys, yo, yf, yf_stride);
+  const unsigned gy = (unsigned)((cout + 16 * JN - 1) / (16 * JN));
+  const int resident = resident_workgroups((const void*)conv3x3_patch_kernel<JN, MASKED, ONE>, 64 * PT / PR);
+  // as many columns of tiles as the CUs hold at once with all their channel groups: a
+  // workgroup that has to wait for a place comes on top (518 for 325 us, 384 of 128
+  // channels at 4 x 320x240, with 516 of them for 512 places)
+  unsigned columns = tiles;
+  if (resident > 0) {
+    const unsigned most = (unsigned)resident / 8 / gy * 8;
+    columns = std::min(tiles, most ? most : std::max(1u, (unsigned)resident / gy));
+  }
+  const unsigned grid = (columns + 7) / 8 * 8 * gy;
+  hipLaunchKernelGGL((conv3x3_patch_kernel<JN, MASKED, ONE>), dim3(grid), dim3(64 * PT / PR), 0, s, x1, x2,
+                     mask, n, h, w, wp, cout, cin, bias, relu, yp, ys, yo, yf, yf_stride, (int)columns);
   return hipGetLastError();
 }
 
@@ -1419,21 +1472,27 @@ hipError_t nn_conv3x3(const gs_act* x1, const gs_act* x2, const gs_act* mask, co
   auto* yp = y ? static_cast<uint16_t*>(y->data) : nullptr;
   const int ys = y ? y->stride : 0, yo = y ? y->offset : 0;
   const auto* wp = static_cast<const uint16_t*>(w);
-  if (cin % 8 == 0 && x1->c % 8 == 0) {
+  // (pixels of an image are 32-bit numbers in the kernels of the first branch)
+  const bool image32 = (int64_t)x1->h * x1->w < (int64_t)1 << 31;
+  if (cin % 8 == 0 && x1->c % 8 == 0 && image32) {
     const unsigned tiles = (unsigned)(x1->n * ((x1->h + PT - 1) / PT) * ((x1->w + PT - 1) / PT));
-    // 32 output channels per workgroup up to 32 channels, for an odd number
-    // of 32-channel groups (96 channels in 64-channel tiles would waste a
-    // quarter of the products), and also where 64-channel workgroups would
-    // number fewer than 1,024: twice the workgroups, and at 49 KB of LDS three
-    // fit a CU (72 KB: two); measured 3% faster on the forward pass of four
-    // 640x480 images, and the 96-channel backward-data call 2% of the backward
+    // 32 output channels per workgroup up to 32 channels, for an odd number of
+    // 32-channel groups (96 in 64-channel workgroups would waste a quarter of the
+    // products), and where 64-channel workgroups would number fewer than 1,024, two for
+    // each of the 512 places: half as much to a workgroup fills the places of a small
+    // layer and leaves less in the last turn of a middling one, while in a large one
+    // both halves of the channels would read the input.  The line at 512, 1,024 or
+    // 2,048 (us): 320x240, 128 -> 128 31, 28, 28; 8 x 160x120, 64 -> 64 21, 18, 18 and
+    // 384 -> 128 133, 130, 155.
     const bool narrow =
         cout <= 32 || cout % 64 == 32 || tiles * (unsigned)((cout + 63) / 64) < 1024u;
-#define GS_PATCH(B, M)                                                                     \
-  launch_patch<B, M>(view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias, \
-                     relu, yp, ys, yo, yf, yf_stride, tiles, s)
-    if (narrow) return mask ? GS_PATCH(32, true) : GS_PATCH(32, false);
-    return mask ? GS_PATCH(64, true) : GS_PATCH(64, false);
+    const bool one = cin <= PCC;
+#define GS_PATCH(J, M, O)                                                                     \
+  launch_patch<J, M, O>(view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias, \
+                        relu, yp, ys, yo, yf, yf_stride, tiles, s)
+    if (narrow && one) return mask ? GS_PATCH(2, true, true) : GS_PATCH(2, false, true);
+    if (narrow) return mask ? GS_PATCH(2, true, false) : GS_PATCH(2, false, false);
+    return mask ? GS_PATCH(4, true, false) : GS_PATCH(4, false, false);
 #undef GS_PATCH
   }
   const unsigned ntile = (unsigned)((cout + 63) / 64);

@@ -62,3 +62,51 @@ def test_wgrad_edges(gs, case):
         for got in (dw, only):
             assert (np.abs(np_(got[k]) - ref.numpy()) <= 1e-5 * scale.numpy() + 1e-7).all(), (case, k)
     assert (np.abs(np_(db) - (flat.sum(0) + 1.0).numpy()) <= 1e-5 * (flat.abs().sum(0) + 1.0).numpy()).all()
+
+
+CONV_CASES = [
+    # (n, h, w, cin1, cin2, cout, masked, channel offset of the output)
+    (1, 1, 1, 8, 0, 8, False, 0),
+    (1, 16, 16, 32, 0, 32, False, 0),      # exactly one tile
+    (2, 17, 33, 32, 0, 32, True, 8),       # a row and a column past it, a channel slice
+    (1, 5, 40, 64, 32, 32, False, 0),      # three chunks, concatenated
+    (1, 20, 20, 32, 0, 96, True, 0),       # 96 channels at a time
+    (1, 18, 15, 24, 0, 72, True, 0),       # of which 72
+    (1, 9, 70, 32, 0, 65, False, 0),       # channel counts that are not multiples of 8:
+    (1, 9, 30, 40, 0, 20, False, 0),       # element by element
+    (1, 9, 30, 32, 0, 32, False, 3),       # and an output that is not 16-byte aligned
+    (2, 30, 21, 128, 64, 64, True, 0),
+    (3, 120, 160, 32, 0, 128, True, 0),    # 64 channels at a time
+]
+
+
+@pytest.mark.parametrize("case", CONV_CASES)
+def test_conv_edges(gs, case):
+    print(case, flush=True)
+    n, h, w, c1, c2, cout, masked, off = case
+    cin = c1 + c2
+    rng = np.random.default_rng(sum(case))
+    x = _bf16(rng.normal(size=(n, h, w, cin)))
+    m = _bf16(np.where(rng.random((n, h, w, cin)) < 0.1, -0.0, rng.normal(size=(n, h, w, cin))))
+    wt = _bf16(rng.normal(size=(9, cout, cin)) / np.sqrt(9 * cin))
+    b = torch.as_tensor(rng.normal(size=cout).astype(np.float32))
+    stride = (cout + off + 7) // 8 * 8 + 8
+    xa, xb = _act(gs, x[..., :c1]), _act(gs, x[..., c1:]) if c2 else None
+    mask = _act(gs, m) if masked else None
+    xm = x.double() * ((m > 0).double() if masked else 1.0)
+    pad = torch.nn.functional.pad(xm, (0, 0, 1, 1, 1, 1))
+    taps = [pad[:, k // 3:k // 3 + h, k % 3:k % 3 + w] for k in range(9)]
+    ref = sum(t @ wt[k].double().T for k, t in enumerate(taps)) + b.double()
+    scale = (sum(t.abs() @ wt[k].double().abs().T for k, t in enumerate(taps)) + b.double().abs()).numpy()
+    for relu in (False, True):
+        wide = torch.full((n, h, w, stride), -7.0, dtype=torch.bfloat16, device=DEV)
+        yf = torch.full((n * h * w, cout + 3), -7.0, device=DEV)
+        gs.gs_nn_conv3x3(xa, xb, mask, wt.to(DEV), cout, b.to(DEV), relu, gs.Act(wide, cout, off), yf, cout + 3)
+        torch.cuda.synchronize()
+        want = ref.clamp(min=0) if relu else ref
+        got = np_(yf)[:, :cout].reshape(n, h, w, cout)
+        assert (np.abs(got - want.numpy()) <= 1e-5 * scale + 1e-7).all(), case
+        # the bf16 output is the rounding of the float32 one, and nothing beside it is written
+        assert torch.equal(wide[..., off:off + cout].reshape(-1, cout), yf[:, :cout].to(torch.bfloat16))
+        assert (wide[..., :off] == -7).all() and (wide[..., off + cout:] == -7).all()
+        assert (yf[:, cout:] == -7).all()

@@ -277,9 +277,9 @@ size_t gs_bin_sort_workspace_size(int64_t n, const gs_views* views, int64_t capa
  * tiles of each splat's rectangle, scans, emits one key per (splat, tile)
  * in splat-major, row-major order, radix-sorts keys ascending (stable, so
  * equal keys keep ascending value order) and writes per-tile ranges.
- * n_keys_host != NULL: synchronises once to read the key count; if it
- * exceeds bins->capacity, *n_keys_host holds the required capacity, nothing
- * further is enqueued and GS_ERR_CAPACITY is returned.
+ * n_keys_host != NULL: waits once, for the key count (not for the sort); if
+ * it exceeds bins->capacity, *n_keys_host holds the required capacity, no key
+ * is placed, the stream is synchronised and GS_ERR_CAPACITY is returned.
  * n_keys_host == NULL: no synchronisation (capture-safe); keys beyond the
  * capacity are dropped and bins->n_keys reports the full count, which the
  * caller must check against the capacity after the stream completes. */

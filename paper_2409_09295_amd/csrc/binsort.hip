@@ -110,6 +110,7 @@ constexpr int kBinChunk = kBinThreads;                  // splats per binning ch
 constexpr int kBinGrid = 64;                             // binning workgroups per view
 constexpr int kLdsTiles = 8192;                          // largest LDS histogram (tiles)
 constexpr int kSegShort = 1024;                          // longest list of the wavefront sort
+constexpr int kSegFew = 256, kSegFewTiles = 1536;         // the same up to so many tiles
 constexpr int kSegLong = 4096;                           // longest list of the workgroup sort
 constexpr int kSortThreads = 512;                        // threads of a sort workgroup
 constexpr int kSortWaves = kSortThreads / 64;
@@ -747,11 +748,11 @@ __device__ void radix_segment_sort(uint64_t* a, uint64_t* b, int64_t len, uint32
 }
 
 // Grid long_slots + T / kSortWaves.  The first long_slots workgroups take
-// the queued lists longer than kSegShort (all wavefronts of a workgroup up to
+// the queued lists longer than seg_short (all wavefronts of a workgroup up to
 // kSegLong pairs, else the radix sort, whose pair buffers are `staged` itself
 // and `spare`); they are dispatched first, so the long lists run beside the
 // short ones.  In every later workgroup each wavefront sorts one tile's list
-// of up to kSegShort pairs in registers.
+// of up to seg_short <= kSegShort pairs in registers.
 template <typename K>
 __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(const uint32_t* __restrict__ ranges,
                                                                 int n_tiles,
@@ -761,7 +762,8 @@ __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(const uint32_t* 
                                                                 uint32_t* __restrict__ vals,
                                                                 const uint32_t* __restrict__ long_list,
                                                                 const uint32_t* __restrict__ n_long,
-                                                                int long_slots) {
+                                                                int long_slots,
+                                                                int seg_short) {
   __shared__ uint64_t s_mem[kSegLong + 128];   // pairs, or the radix sort's digit counts
   if (blockIdx.x < (unsigned)long_slots) {
     uint32_t* s_cnt = reinterpret_cast<uint32_t*>(s_mem + kSegLong);
@@ -771,7 +773,11 @@ __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(const uint32_t* 
       const uint32_t tile = long_list[q];
       const uint32_t s = ranges[2 * (int64_t)tile], e = ranges[2 * (int64_t)tile + 1];
       const int64_t len = (int64_t)e - (int64_t)s;
-      if (len <= kSegLong / 2) {
+      if (len <= kSortThreads) {
+        block_segment_sort<1>(staged, s, (int)len, tile, keys, vals, s_mem);
+      } else if (len <= 2 * kSortThreads) {
+        block_segment_sort<2>(staged, s, (int)len, tile, keys, vals, s_mem);
+      } else if (len <= kSegLong / 2) {
         block_segment_sort<kSegLong / (2 * kSortThreads)>(staged, s, (int)len, tile, keys, vals, s_mem);
       } else if (len <= kSegLong) {
         block_segment_sort<kSegLong / kSortThreads>(staged, s, (int)len, tile, keys, vals, s_mem);
@@ -789,7 +795,7 @@ __global__ __launch_bounds__(kSortThreads) void seg_sort_kernel(const uint32_t* 
   const uint32_t s = ranges[2 * (int64_t)tile], e = ranges[2 * (int64_t)tile + 1];
   const int64_t len = (int64_t)e - (int64_t)s;   // 0 for every tile on overflow
   const uint32_t t = (uint32_t)tile;
-  if (len <= 0 || len > kSegShort) return;
+  if (len <= 0 || len > seg_short) return;
   if (len <= 64) wave_segment_sort<1>(staged, s, (int)len, t, keys, vals);
   else if (len <= 128) wave_segment_sort<2>(staged, s, (int)len, t, keys, vals);
   else if (len <= 256) wave_segment_sort<4>(staged, s, (int)len, t, keys, vals);
@@ -1039,7 +1045,7 @@ __global__ __launch_bounds__(1024) void few_scan_kernel(
     uint32_t* __restrict__ ranges, uint32_t* __restrict__ starts, uint64_t* __restrict__ total,
     uint32_t* __restrict__ n_keys, uint64_t* __restrict__ host_count,
     uint32_t* __restrict__ long_list, uint32_t* __restrict__ n_long, uint32_t* __restrict__ queue,
-    uint32_t* __restrict__ order) {
+    uint32_t* __restrict__ order, uint32_t seg_short) {
   constexpr int kPer = kFewTiles / 1024;   // tile c 1024 + thread, c < kPer
   constexpr int kWaves = 16;
   constexpr int kCells = kOrderGroups * kPer * kWaves;   // (group, c, wave), longest group first
@@ -1095,7 +1101,7 @@ __global__ __launch_bounds__(1024) void few_scan_kernel(
       ranges[2 * (int64_t)t] = len ? st : 0u;
       ranges[2 * (int64_t)t + 1] = len ? st + len : 0u;
       starts[t] = st;
-      if (len > (uint32_t)kSegShort) long_list[atomicAdd(&s_long, 1u)] = (uint32_t)t;
+      if (len > seg_short) long_list[atomicAdd(&s_long, 1u)] = (uint32_t)t;
     }
     // the lanes of this wavefront whose tiles share the length group
     const uint32_t g = (uint32_t)length_group(len);
@@ -1278,6 +1284,11 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
     __atomic_store_n(t_count.host, kNoCount, __ATOMIC_RELEASE);
     host_count = t_count.dev;
   }
+  // Lists that a whole workgroup sorts: with few tiles from 256 pairs up, where a
+  // wavefront alone takes 10 to 20 us while CUs idle (whole call, 256 | 1,024: 300 tiles
+  // of 600 pairs 28 | 38 us, 1,200 of 230 34 | 36; 2,400 of 350 63 | 57, 9,600 of 290
+  // 129 | 90).
+  const int seg_short = few && T <= kSegFewTiles ? kSegFew : kSegShort;
   const dim3 few_grid((unsigned)P.chunks, (unsigned)vt.n_views);
   if (few) {
 #define GS_GATHER(E)                                                                          \
@@ -1291,7 +1302,7 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
                        0, s, matrix, (int)P.chunks, T, counts);
     hipLaunchKernelGGL(few_scan_kernel, dim3(1), dim3(1024), 0, s, counts, T, P.capacity,
                        bins.ranges, starts, total, bins.n_keys, host_count, long_list, n_long,
-                       bins.queue, bins.order);
+                       bins.queue, bins.order, (uint32_t)seg_short);
   } else {
     // 1. the splats that touch a tile, per view; keys per (chunk, tile), per
     // tile, the segments and the key count
@@ -1329,11 +1340,11 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
     if (bins.keys)
       hipLaunchKernelGGL(seg_sort_kernel<uint64_t>, dim3(sblocks), dim3(kSortThreads), 0, s,
                          bins.ranges, T, staged, spare, bins.keys, bins.values, long_list, n_long,
-                         long_slots);
+                         long_slots, seg_short);
     else
       hipLaunchKernelGGL(seg_sort_kernel<uint32_t>, dim3(sblocks), dim3(kSortThreads), 0, s,
                          bins.ranges, T, staged, spare, (uint32_t*)nullptr, bins.values, long_list,
-                         n_long, long_slots);
+                         n_long, long_slots, seg_short);
   }
   // 3. launch order of the compositing grids (from the ranges; on overflow
   // they are all empty and this is the identity)

@@ -91,3 +91,19 @@ def test_short_path_views_of_several_sizes(gs, n, sizes):
         s = int(r[r[:, 1] > r[:, 0]].min())
         assert torch.equal(bins.values[s:s + k] - v * n, alone.values[:k])
         first += tiles
+
+
+@pytest.mark.parametrize("n", [255, 256, 257, 512, 513, 1024, 1025, 2048, 2049, 4096, 4097])
+def test_short_path_list_lengths(gs, n):
+    """One tile, every list length at which another sort takes over."""
+    print(f"n {n}", flush=True)
+    cam = scenes.pinhole(16, 16, 12.0)
+    sp = scenes.random_splats(n, [cam], seed=n, sigma_px=(0.6, 8.0), cull_frac=0.0, depth_ties=0.1)
+    sp.xy[...] = np.clip(sp.xy, 1.0, 15.0)
+    pad = LIMIT + 1 - n
+    z = lambda a: np.concatenate([a, np.zeros((1, pad) + a.shape[2:], a.dtype)], 1)
+    many = scenes.SplatSet(z(sp.xy), z(sp.conic_opacity), z(sp.rgb_depth), z(sp.radius), sp.cams)
+    a, ca, _ = _bin(gs, sp, cam, n)
+    b, cb, _ = _bin(gs, many, cam, n)
+    assert ca == cb == n
+    assert torch.equal(a.values, b.values) and torch.equal(a.keys, b.keys)

@@ -1472,9 +1472,7 @@ hipError_t nn_conv3x3(const gs_act* x1, const gs_act* x2, const gs_act* mask, co
   auto* yp = y ? static_cast<uint16_t*>(y->data) : nullptr;
   const int ys = y ? y->stride : 0, yo = y ? y->offset : 0;
   const auto* wp = static_cast<const uint16_t*>(w);
-  // (pixels of an image are 32-bit numbers in the kernels of the first branch)
-  const bool image32 = (int64_t)x1->h * x1->w < (int64_t)1 << 31;
-  if (cin % 8 == 0 && x1->c % 8 == 0 && image32) {
+  if (cin % 8 == 0 && x1->c % 8 == 0) {
     const unsigned tiles = (unsigned)(x1->n * ((x1->h + PT - 1) / PT) * ((x1->w + PT - 1) / PT));
     // 32 output channels per workgroup up to 32 channels, for an odd number of
     // 32-channel groups (96 in 64-channel workgroups would waste a quarter of the
@@ -1524,11 +1522,17 @@ hipError_t nn_conv3x3_wgrad(const gs_act* x1, const gs_act* x2, const gs_act* dz
   const int cin = x1->c + (x2 ? x2->c : 0);
   const int cout = dz->c;
   const int64_t npix = (int64_t)x1->n * x1->h * x1->w;
-  if (cin % 8 == 0 && x1->c % 8 == 0 && cout % 8 == 0 &&
-      (int64_t)x1->h * x1->w < (int64_t)1 << 31) {   // pixels of an image: 32-bit numbers there
-    // 32 output channels per workgroup up to 32, else 64; 32 input channels for
-    // an odd number of 32-channel groups, else 64 (with 64 output channels)
-    const bool one_co = cout <= 32, one_ci = one_co || (cin + 31) / 32 % 2 == 1;
+  if (cin % 8 == 0 && x1->c % 8 == 0 && cout % 8 == 0) {
+    // 32 x 32 channels per workgroup up to 32 output channels and for little work:
+    // fewer runs share a pair then, and with them go the closing adds, which bound
+    // small layers; else 64 output channels, and 64 input channels unless these are
+    // an odd number of 32-channel groups, which halves what is staged per product.
+    // 32 x 32 against 64 x 64 (us, millions of pixels and channel pairs): 160x120,
+    // 128 -> 128 (0.3) 23 and 30; 320x240, 128 -> 128 (1.2) 50 and 58; 160x120, 256 ->
+    // 256 (1.2) 48 and 51, as four 80x60 58 and 55; 8 x 160x120, 192 -> 64 (1.8) 70
+    // and 67, 128 -> 128 (2.5) 86 and 81; 320x240, 256 -> 256 (4.9) 159 and 106.
+    const int64_t work = npix * ((cin + 31) / 32) * ((cout + 31) / 32);
+    const bool one_co = cout <= 32 || work <= 1250000, one_ci = one_co || (cin + 31) / 32 % 2 == 1;
     const int rows = one_co ? 8 : 4;   // per step
     const int steps = x1->n * ((x1->w + WG_W - 1) / WG_W) * ((x1->h + rows - 1) / rows);
     const int ci_groups = one_ci ? (cin + 31) / 32 : (cin + 63) / 64;

@@ -31,6 +31,8 @@ WGRAD_CASES = [
     (1, 6, 50, 40, 24, 72, False),      # groups cut short on both sides
     (1, 3, 7, 24, 0, 40, True),
     (9, 16, 96, 64, 64, 64, True),      # runs that cross strips and images
+    (1, 33, 70, 768, 0, 800, True),     # enough work for 64 x 64 channels a workgroup
+    (2, 30, 40, 712, 24, 776, True),    # and for 64 x 32
 ]
 
 

@@ -81,6 +81,56 @@ __device__ __forceinline__ Reduced9 wave_reduce9(float v0, float v1, float v2, f
   return r;
 }
 
+// The lane's pixel at a splat of the reverse walk (ok: it blends it; alpha, raw, G and
+// dx, dy as eval_alpha_at returns them): adds the nine partials to g and moves T and
+// sdc, the projection on dC of the colour behind, in front of the splat.
+__device__ __forceinline__ void add_pixel(bool ok, float alpha, float raw, float G, float dx,
+                                          float dy, const float4& app, float blue, float dC0,
+                                          float dC1, float dC2, float& T, float& sdc,
+                                          float (&g)[9]) {
+  const float a = ok ? alpha : 0.0f;
+  const float Tk = T * __builtin_amdgcn_rcpf(1.0f - a);
+  const float wgt = a * Tk;
+  const float dot = __builtin_fmaf(
+      blue, dC2, __builtin_fmaf(app.w, dC1, __builtin_fmaf(app.z, dC0, -sdc)));
+  const float dalpha = Tk * dot;   // (c - S) . dL/dC
+  // colour behind the next splat in front: S + alpha (c - S)
+  sdc = __builtin_fmaf(a, dot, sdc);
+  T = Tk;
+  // below the 0.99 clamp alpha = o G: d alpha/do = G, d alpha/dpower = alpha
+  const float live = (ok && raw <= kAlphaMax) ? dalpha : 0.0f;
+  const float gP = a * live;   // dL/dpower
+  const float gdx = gP * dx, gdy = gP * dy;
+  // d power/du = Q00 dx + Q01 dy (and likewise v): the conic factor is
+  // the same for every pixel, so only sum(gP d) is accumulated here
+  g[0] += gdx;
+  g[1] += gdy;
+  g[2] += gdx * dx;
+  g[3] += gdx * dy;
+  g[4] += gdy * dy;
+  g[5] += G * live;
+  g[6] += wgt * dC0;
+  g[7] += wgt * dC1;
+  g[8] += wgt * dC2;
+}
+
+// Sums a wavefront's nine partials and adds them to the record whose index are the
+// bits of acc (wavefront-uniform).  wave_reduce9 leaves value {0, 2, 1, 3}[r] in row
+// r = lane / 16 of q0, 4 + {0, 2, 1, 3}[r] in that of q1 and value 8 in lane 63 of q2:
+// one atomic instruction adds all nine from lanes 16 r, 16 r + 1 and 63.
+__device__ __forceinline__ void add_record(const float (&g)[9], float* __restrict__ grad2d,
+                                           float acc, int lane) {
+  const int row = lane >> 4, col16 = lane & 15;
+  const int red_off0 = (row == 0) ? 0 : (row == 1) ? 2 : (row == 2) ? 1 : 3;
+  const bool red_q0 = col16 == 0, red_q1 = col16 == 1, red_q2 = lane == 63;
+  const int red_off = red_q0 ? red_off0 : red_q1 ? red_off0 + 4 : 8;
+  const Reduced9 r = wave_reduce9(g[0], g[1], g[2], g[3], g[4], g[5], g[6], g[7], g[8]);
+  const uint32_t rec = __builtin_amdgcn_readfirstlane(__float_as_uint(acc));
+  float* dst = grad2d + (int64_t)rec * 9;   // wave-uniform
+  const float val = red_q0 ? r.q0 : red_q1 ? r.q1 : r.q2;
+  if (red_q0 || red_q1 || red_q2) unsafeAtomicAdd(dst + red_off, val);
+}
+
 // SPL: splats each thread stages per LDS batch (1 or 2).
 template <int PPL, int SPL, bool Q>
 __global__ __launch_bounds__(kBlock / PPL) void render_bwd_kernel(
@@ -110,16 +160,6 @@ __global__ __launch_bounds__(kBlock / PPL) void render_bwd_kernel(
     const int lt = tile - vi.tile_base;
     const int tx = lt % vi.tiles_x, ty = lt / vi.tiles_x;
     const int lane = threadIdx.x & 63;
-    // where wave_reduce9 leaves each value: row r = lane / 16 of q0 holds value
-    // {0, 2, 1, 3}[r] and of q1 value 4 + {0, 2, 1, 3}[r]; lane 63 of q2 holds
-    // value 8
-    // One atomic instruction adds all nine: lane 16 r takes q0's row total,
-    // lane 16 r + 1 q1's, lane 63 the ninth value.
-    const int row = lane >> 4, col16 = lane & 15;
-    const int red_off0 = (row == 0) ? 0 : (row == 1) ? 2 : (row == 2) ? 1 : 3;
-    const bool red_q0 = col16 == 0, red_q1 = col16 == 1, red_q2 = lane == 63;
-    const int red_off = red_q0 ? red_off0 : red_q1 ? red_off0 + 4 : 8;
-
     // pixel k of a lane lies in column k % NC (see the forward kernel)
     constexpr int NC = PPL == 4 ? 2 : 1;
     // sdc: (colour behind the current splat) . dL/dC of the pixel
@@ -212,8 +252,9 @@ __global__ __launch_bounds__(kBlock / PPL) void render_bwd_kernel(
           // Per pixel slot, branch-free over the wave: a lane whose pixel does
           // not blend this splat takes alpha = 0, which leaves T and S exactly
           // as they were and contributes exact zeros.
-          float g0 = -0.0f, g1 = -0.0f, g2 = -0.0f, g3 = -0.0f, g4 = -0.0f, g5 = -0.0f,
-                g6 = -0.0f, g7 = -0.0f, g8 = -0.0f;   // -0 + x == x exactly
+          float g[9];
+#pragma unroll
+          for (int c = 0; c < 9; ++c) g[c] = -0.0f;   // -0 + x == x exactly
           bool started = false;
           ColumnTerms ct[NC];
 #pragma unroll
@@ -229,38 +270,169 @@ __global__ __launch_bounds__(kBlock / PPL) void render_bwd_kernel(
                 eval_alpha_at<true>(ct[k % NC], geo, app, fpy[k], alpha, raw, G, dy) &&
                 pos < last[k];
             if (!__ballot(ok)) continue;
-            const float a = ok ? alpha : 0.0f;
-            const float Tk = T[k] * __builtin_amdgcn_rcpf(1.0f - a);
-            const float wgt = a * Tk;
-            const float dot = __builtin_fmaf(
-                ext.x, dC2[k], __builtin_fmaf(app.w, dC1[k], __builtin_fmaf(app.z, dC0[k], -sdc[k])));
-            const float dalpha = Tk * dot;   // (c - S) . dL/dC
-            // colour behind the next splat in front: S + alpha (c - S)
-            sdc[k] = __builtin_fmaf(a, dot, sdc[k]);
-            T[k] = Tk;
-            // below the 0.99 clamp alpha = o G: d alpha/do = G, d alpha/dpower = alpha
-            const float live = (ok && raw <= kAlphaMax) ? dalpha : 0.0f;
-            const float gP = a * live;   // dL/dpower
-            const float gdx = gP * dx, gdy = gP * dy;
-            // d power/du = Q00 dx + Q01 dy (and likewise v): the conic factor is
-            // the same for every pixel, so only sum(gP d) is accumulated here
-            const float v2 = gdx * dx, v3 = gdx * dy, v4 = gdy * dy, v5 = G * live;
-            const float v6 = wgt * dC0[k], v7 = wgt * dC1[k], v8 = wgt * dC2[k];
-            g0 += gdx; g1 += gdy; g2 += v2; g3 += v3; g4 += v4; g5 += v5; g6 += v6; g7 += v7;
-            g8 += v8;
+            add_pixel(ok, alpha, raw, G, dx, dy, app, ext.x, dC0[k], dC1[k], dC2[k], T[k], sdc[k], g);
             started = true;
           }
           if (started) {
-            const Reduced9 r = wave_reduce9(g0, g1, g2, g3, g4, g5, g6, g7, g8);
-            const uint32_t acc = __builtin_amdgcn_readfirstlane(__float_as_uint(ext.w));
-            float* dst = grad2d + (int64_t)acc * 9;   // wave-uniform
-            const float val = red_q0 ? r.q0 : red_q1 ? r.q1 : r.q2;
-            if (red_q0 || red_q1 || red_q2) unsafeAtomicAdd(dst + red_off, val);
+            add_record(g, grad2d, ext.w, lane);
           }
         }
       }
     }
     if constexpr (!Q) break;
+  }
+}
+
+// The reverse walk for launches of few tiles: a workgroup takes one quadrant of a tile,
+// and its four wavefronts a quarter each of the list up to the quadrant's last blended
+// splat.  A quarter cannot start before its pixels' T and the colour behind are known.
+// Both follow from the quarters behind: over one, T in front is T behind / P, P the
+// product of its 1 - alpha, and the projected colour C + P times the one behind, C its
+// own composite over black.  So a quarter is walked twice: for P and C (not the front
+// one), about a third of the work of a step of the second walk, and, after an exchange
+// through LDS, for the partials.
+//
+// Why: one wavefront per quadrant issues an instruction every five cycles or so, and
+// three to four of them share a SIMD without slowing each other, but 300 tiles leave it
+// with one, and two on the 44 CUs that hold two tiles.  (Four wavefronts per quadrant of
+// whole tiles, 1,024 threads, gained nothing: those CUs had the work of two.)
+// Kernel alone: 300 tiles of the tracking step 66 -> 43 us, 320 of a local one 39 -> 30.
+// Whole backward, one wavefront | four (us): 12 tiles 60 | 32, 300 of 100,000 Gaussians
+// 123 | 72, 768 97 | 71, 945 88 | 77, 1,200 72 | 86 and, with long lists, 111 | 102.
+constexpr int kSplit = 4;          // quarters of a list: wavefronts
+constexpr int kSplitTiles = 1000;  // most tiles of such a launch
+constexpr int kSplitStage = 128;   // splats a wavefront stages at a time
+
+__global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
+    ViewTable vt, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ values,
+    const uint32_t* __restrict__ order, const float2* __restrict__ xy,
+    const float4* __restrict__ co, const float4* __restrict__ rd, float3 bg,
+    const float* __restrict__ dL_dimage, const float* __restrict__ final_T,
+    const uint32_t* __restrict__ n_contrib, float* __restrict__ grad2d) {
+  constexpr int kWords = kSplitStage / 64;
+  constexpr int kGroup = 4;   // splats of the first walk evaluated side by side
+  __shared__ StagedSplat s_splats[kSplit][kSplitStage];
+  __shared__ float2 s_pc[kSplit][64];   // (P, C) of the quarter and pixel
+  const int lane = threadIdx.x & 63;
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  StagedSplat* s_splat = s_splats[part];
+  const int q = blockIdx.x & 3;
+  const int tile = order ? (int)order[blockIdx.x >> 2] : (int)(blockIdx.x >> 2);
+  const int v = find_view(vt, tile);
+  const ViewInfo& vi = vt.v[v];
+  const int lt = tile - vi.tile_base;
+  const int tx = lt % vi.tiles_x, ty = lt / vi.tiles_x;
+  const int px = tx * kTile + (q & 1) * 8 + (lane & 7), py = ty * kTile + (q >> 1) * 8 + (lane >> 3);
+  const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
+  float T = 1.0f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f, sdc = 0.f;
+  uint32_t last = 0;
+  if (px < vi.width && py < vi.height) {
+    const int64_t plane = (int64_t)vi.width * vi.height, off = (int64_t)py * vi.width + px;
+    const float* gimg = dL_dimage + 3 * vi.pix_base;
+    dC0 = gimg[off];
+    dC1 = gimg[plane + off];
+    dC2 = gimg[2 * plane + off];
+    T = final_T[vi.pix_base + off];
+    sdc = bg.x * dC0 + bg.y * dC1 + bg.z * dC2;
+    last = n_contrib[vi.pix_base + off];
+  }
+  uint32_t wave_last = last;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1)
+    wave_last = max(wave_last, (uint32_t)__shfl_xor((int)wave_last, d, 64));
+  const uint32_t s = ranges[2 * tile], e = ranges[2 * tile + 1];
+  // n_contrib never exceeds the tile's list length for a matching forward; the clamp
+  // keeps every list read inside [s, e) regardless
+  const uint32_t len = min((uint32_t)__builtin_amdgcn_readfirstlane(wave_last), e > s ? e - s : 0u);
+  if (len == 0) return;   // the whole workgroup: its wavefronts hold the same pixels
+  const uint32_t quarter = (len + kSplit - 1) / kSplit;
+  const uint32_t beg = min(len, part * quarter), end = min(len, beg + quarter);
+
+  uint64_t reach[kWords];   // staged splats that reach the quadrant (wavefront-uniform)
+  auto stage = [&](uint32_t at) {   // list positions at .. (of this wavefront's quarter)
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) {
+      const uint32_t k = at + 64 * w + lane;
+      uint32_t r = 0;
+      if (k < end)
+        r = stage_splat(values[s + k], xy, co, rd, tx * kTile, ty * kTile, vi.width, vi.height,
+                        s_splat[64 * w + lane]);
+      reach[w] = uniform_u64(__ballot((r >> q) & 1u));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  // first positions of the staged batches, back to front
+  const uint32_t n_batches = (end - beg + kSplitStage - 1) / kSplitStage;
+
+  float P = 1.0f, C = 0.0f;
+  if (part > 0) {
+    for (uint32_t b = n_batches; b-- > 0;) {
+      const uint32_t at = beg + b * kSplitStage;
+      stage(at);
+#pragma unroll
+      for (int w = kWords - 1; w >= 0; --w) {
+        uint64_t m = reach[w];
+        while (m) {
+          float a[kGroup], dot[kGroup];
+          int bit = 0;
+#pragma unroll
+          for (int i = 0; i < kGroup; ++i) {
+            const bool some = m != 0;   // else the previous splat again, not blended
+            if (some) bit = 63 - __builtin_clzll(m);
+            m &= ~(uint64_t(1) << bit);
+            const int j = 64 * w + bit;
+            const float4 geo = s_splat[j].geo, app = s_splat[j].app;
+            float alpha, raw, G, dy;
+            const bool ok =
+                eval_alpha_at<true>(column_terms(geo, fpx), geo, app, fpy, alpha, raw, G, dy) &&
+                some && at + j < last;
+            a[i] = ok ? alpha : 0.0f;
+            dot[i] = __builtin_fmaf(s_splat[j].ext.x, dC2,
+                                    __builtin_fmaf(app.w, dC1, app.z * dC0));
+          }
+#pragma unroll
+          for (int i = 0; i < kGroup; ++i) {
+            C = __builtin_fmaf(a[i], dot[i] - C, C);
+            P *= 1.0f - a[i];
+          }
+        }
+      }
+    }
+  }
+  s_pc[part][lane] = make_float2(P, C);
+  __syncthreads();
+  float behind = 1.0f;
+  for (int h = kSplit - 1; h > part; --h) {
+    const float2 pc = s_pc[h][lane];
+    behind *= pc.x;
+    sdc = __builtin_fmaf(pc.x, sdc, pc.y);
+  }
+  T /= behind;
+  for (uint32_t b = n_batches; b-- > 0;) {
+    const uint32_t at = beg + b * kSplitStage;
+    if (n_batches > 1 || part == 0) stage(at);   // else it is still there
+#pragma unroll
+    for (int w = kWords - 1; w >= 0; --w) {
+      uint64_t m = reach[w];
+      while (m) {
+        const int bit = 63 - __builtin_clzll(m);
+        m &= ~(uint64_t(1) << bit);
+        const int j = 64 * w + bit;
+        const float4 geo = s_splat[j].geo, app = s_splat[j].app, ext = s_splat[j].ext;
+        const ColumnTerms ct = column_terms(geo, fpx);
+        float alpha, raw, G, dy;
+        const bool ok =
+            eval_alpha_at<true>(ct, geo, app, fpy, alpha, raw, G, dy) && at + j < last;
+        if (!__ballot(ok)) continue;
+        float g[9];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) g[c] = -0.0f;
+        add_pixel(ok, alpha, raw, G, ct.dx, dy, app, ext.x, dC0, dC1, dC2, T, sdc, g);
+        add_record(g, grad2d, ext.w, lane);
+      }
+    }
   }
 }
 
@@ -664,8 +836,16 @@ hipError_t launch_render_bwd(const gs_gaussians& g, const gs_projected& p, const
     if (set_ppl == 0 && ppl == 2 && tuning(GS_TUNE_BWD_STAGE) == 0) spl = 1;
 #define GS_BWD(P, S) \
   launch_bwd<P, S>(sched, bins, vt, xy, co, rd, bg, dL_dimage, final_T, n_contrib, grad2d, s)
+    // few tiles: lists in quarters (the figures stand at the kernel)
+    const bool split = set_ppl == 0 && tuning(GS_TUNE_BWD_STAGE) == 0 &&
+                       sched < GS_SCHEDULE_PERSISTENT && vt.n_tiles <= kSplitTiles;
     kernel_event_start(GS_KERNEL_RENDER_BWD, s);
-    if (ppl == 4) {
+    if (split) {
+      const TileSchedule sc = tile_schedule(sched, bins, GS_QUEUE_BWD, vt.n_tiles, 0);
+      hipLaunchKernelGGL(render_bwd_split_kernel, dim3(4 * (unsigned)vt.n_tiles),
+                         dim3(64 * kSplit), 0, s, vt, bins.ranges, bins.values, sc.order, xy, co, rd,
+                         bg, dL_dimage, final_T, n_contrib, grad2d);
+    } else if (ppl == 4) {
       if (spl == 2) GS_BWD(4, 2); else GS_BWD(4, 1);
     } else if (ppl == 2) {
       if (spl == 2) GS_BWD(2, 2); else GS_BWD(2, 1);

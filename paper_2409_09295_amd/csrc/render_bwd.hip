@@ -285,18 +285,23 @@ __global__ __launch_bounds__(kBlock / PPL) void render_bwd_kernel(
 
 // The reverse walk for launches of few tiles: a workgroup takes one quadrant of a tile,
 // and its four wavefronts a quarter each of the list up to the quadrant's last blended
-// splat.  A quarter cannot start before its pixels' T and the colour behind are known.
-// Both follow from the quarters behind: over one, T in front is T behind / P, P the
-// product of its 1 - alpha, and the projected colour C + P times the one behind, C its
-// own composite over black.  So a quarter is walked twice: for P and C (not the front
-// one), about a third of the work of a step of the second walk, and, after an exchange
-// through LDS, for the partials.
+// splat.  A quarter cannot start before the T and the colour behind its pixels are
+// known.  Both follow from the quarters: with P the product of a quarter's 1 - alpha and
+// C its own projected composite over black, T behind a quarter is the product of the P
+// up to it, and the projected colour in front of one is C + P times the colour behind.
+// So a quarter is walked twice: for P and C, about a third of the work of a step of the
+// second walk, and, after an exchange through LDS, for the partials.  P and C are
+// float64 with the products under them (dC of an L1 loss is the same at every pixel but
+// for the sign, and so would be a rounding of c . dC), and T comes from the front: T taken from final_T and the quarters behind
+// carried the roundings of the forward's whole list (a walk without quarters recovers
+// each T that the forward held almost exactly, since a division by the factor just
+// multiplied rounds back).
 //
 // Why: one wavefront per quadrant issues an instruction every five cycles or so, and
 // three to four of them share a SIMD without slowing each other, but 300 tiles leave it
 // with one, and two on the 44 CUs that hold two tiles.  (Four wavefronts per quadrant of
 // whole tiles, 1,024 threads, gained nothing: those CUs had the work of two.)
-// Kernel alone: 300 tiles of the tracking step 66 -> 43 us, 320 of a local one 39 -> 30.
+// Kernel alone: 300 tiles of the tracking step 66 -> 44 us, 320 of a local one 39 -> 31.
 // Whole backward, one wavefront | four (us): 12 tiles 60 | 32, 300 of 100,000 Gaussians
 // 123 | 72, 768 97 | 71, 945 88 | 77, 1,200 72 | 86 and, with long lists, 111 | 102.
 constexpr int kSplit = 4;          // quarters of a list: wavefronts
@@ -307,12 +312,12 @@ __global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
     ViewTable vt, const uint32_t* __restrict__ ranges, const uint32_t* __restrict__ values,
     const uint32_t* __restrict__ order, const float2* __restrict__ xy,
     const float4* __restrict__ co, const float4* __restrict__ rd, float3 bg,
-    const float* __restrict__ dL_dimage, const float* __restrict__ final_T,
-    const uint32_t* __restrict__ n_contrib, float* __restrict__ grad2d) {
+    const float* __restrict__ dL_dimage, const uint32_t* __restrict__ n_contrib,
+    float* __restrict__ grad2d) {
   constexpr int kWords = kSplitStage / 64;
   constexpr int kGroup = 4;   // splats of the first walk evaluated side by side
   __shared__ StagedSplat s_splats[kSplit][kSplitStage];
-  __shared__ float2 s_pc[kSplit][64];   // (P, C) of the quarter and pixel
+  __shared__ double2 s_pc[kSplit][64];   // (P, C) of the quarter and pixel
   const int lane = threadIdx.x & 63;
   const int part = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   StagedSplat* s_splat = s_splats[part];
@@ -324,7 +329,7 @@ __global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
   const int tx = lt % vi.tiles_x, ty = lt / vi.tiles_x;
   const int px = tx * kTile + (q & 1) * 8 + (lane & 7), py = ty * kTile + (q >> 1) * 8 + (lane >> 3);
   const float fpx = (float)px + 0.5f, fpy = (float)py + 0.5f;
-  float T = 1.0f, dC0 = 0.f, dC1 = 0.f, dC2 = 0.f, sdc = 0.f;
+  float dC0 = 0.f, dC1 = 0.f, dC2 = 0.f, sdc = 0.f;
   uint32_t last = 0;
   if (px < vi.width && py < vi.height) {
     const int64_t plane = (int64_t)vi.width * vi.height, off = (int64_t)py * vi.width + px;
@@ -332,7 +337,6 @@ __global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
     dC0 = gimg[off];
     dC1 = gimg[plane + off];
     dC2 = gimg[2 * plane + off];
-    T = final_T[vi.pix_base + off];
     sdc = bg.x * dC0 + bg.y * dC1 + bg.z * dC2;
     last = n_contrib[vi.pix_base + off];
   }
@@ -366,53 +370,52 @@ __global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
   // first positions of the staged batches, back to front
   const uint32_t n_batches = (end - beg + kSplitStage - 1) / kSplitStage;
 
-  float P = 1.0f, C = 0.0f;
-  if (part > 0) {
-    for (uint32_t b = n_batches; b-- > 0;) {
-      const uint32_t at = beg + b * kSplitStage;
-      stage(at);
+  double P = 1.0, C = 0.0;
+  for (uint32_t b = n_batches; b-- > 0;) {
+    const uint32_t at = beg + b * kSplitStage;
+    stage(at);
 #pragma unroll
-      for (int w = kWords - 1; w >= 0; --w) {
-        uint64_t m = reach[w];
-        while (m) {
-          float a[kGroup], dot[kGroup];
-          int bit = 0;
+    for (int w = kWords - 1; w >= 0; --w) {
+      uint64_t m = reach[w];
+      while (m) {
+        float a[kGroup];
+        double dot[kGroup];
+        int bit = 0;
 #pragma unroll
-          for (int i = 0; i < kGroup; ++i) {
-            const bool some = m != 0;   // else the previous splat again, not blended
-            if (some) bit = 63 - __builtin_clzll(m);
-            m &= ~(uint64_t(1) << bit);
-            const int j = 64 * w + bit;
-            const float4 geo = s_splat[j].geo, app = s_splat[j].app;
-            float alpha, raw, G, dy;
-            const bool ok =
-                eval_alpha_at<true>(column_terms(geo, fpx), geo, app, fpy, alpha, raw, G, dy) &&
-                some && at + j < last;
-            a[i] = ok ? alpha : 0.0f;
-            dot[i] = __builtin_fmaf(s_splat[j].ext.x, dC2,
-                                    __builtin_fmaf(app.w, dC1, app.z * dC0));
-          }
+        for (int i = 0; i < kGroup; ++i) {
+          const bool some = m != 0;   // else the previous splat again, not blended
+          if (some) bit = 63 - __builtin_clzll(m);
+          m &= ~(uint64_t(1) << bit);
+          const int j = 64 * w + bit;
+          const float4 geo = s_splat[j].geo, app = s_splat[j].app;
+          float alpha, raw, G, dy;
+          const bool ok =
+              eval_alpha_at<true>(column_terms(geo, fpx), geo, app, fpy, alpha, raw, G, dy) &&
+              some && at + j < last;
+          a[i] = ok ? alpha : 0.0f;
+          dot[i] = __builtin_fma((double)s_splat[j].ext.x, (double)dC2,
+                                 __builtin_fma((double)app.w, (double)dC1,
+                                               (double)app.z * (double)dC0));
+        }
 #pragma unroll
-          for (int i = 0; i < kGroup; ++i) {
-            C = __builtin_fmaf(a[i], dot[i] - C, C);
-            P *= 1.0f - a[i];
-          }
+        for (int i = 0; i < kGroup; ++i) {
+          C = __builtin_fma((double)a[i], dot[i] - C, C);
+          P = __builtin_fma(-(double)a[i], P, P);
         }
       }
     }
   }
-  s_pc[part][lane] = make_float2(P, C);
+  s_pc[part][lane] = make_double2(P, C);
   __syncthreads();
-  float behind = 1.0f;
-  for (int h = kSplit - 1; h > part; --h) {
-    const float2 pc = s_pc[h][lane];
-    behind *= pc.x;
-    sdc = __builtin_fmaf(pc.x, sdc, pc.y);
-  }
-  T /= behind;
+  double front = 1.0, colour = sdc;
+  for (int h = 0; h <= part; ++h) front *= s_pc[h][lane].x;
+  for (int h = kSplit - 1; h > part; --h)
+    colour = __builtin_fma(s_pc[h][lane].x, colour, s_pc[h][lane].y);
+  float T = (float)front;
+  sdc = (float)colour;
   for (uint32_t b = n_batches; b-- > 0;) {
     const uint32_t at = beg + b * kSplitStage;
-    if (n_batches > 1 || part == 0) stage(at);   // else it is still there
+    if (n_batches > 1) stage(at);   // else it is still there
 #pragma unroll
     for (int w = kWords - 1; w >= 0; --w) {
       uint64_t m = reach[w];
@@ -844,7 +847,7 @@ hipError_t launch_render_bwd(const gs_gaussians& g, const gs_projected& p, const
       const TileSchedule sc = tile_schedule(sched, bins, GS_QUEUE_BWD, vt.n_tiles, 0);
       hipLaunchKernelGGL(render_bwd_split_kernel, dim3(4 * (unsigned)vt.n_tiles),
                          dim3(64 * kSplit), 0, s, vt, bins.ranges, bins.values, sc.order, xy, co, rd,
-                         bg, dL_dimage, final_T, n_contrib, grad2d);
+                         bg, dL_dimage, n_contrib, grad2d);
     } else if (ppl == 4) {
       if (spl == 2) GS_BWD(4, 2); else GS_BWD(4, 1);
     } else if (ppl == 2) {

@@ -380,6 +380,7 @@ __global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
       while (m) {
         float a[kGroup];
         double dot[kGroup];
+        bool ok[kGroup];
         int bit = 0;
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
@@ -389,17 +390,18 @@ __global__ __launch_bounds__(64 * kSplit) void render_bwd_split_kernel(
           const int j = 64 * w + bit;
           const float4 geo = s_splat[j].geo, app = s_splat[j].app;
           float alpha, raw, G, dy;
-          const bool ok =
-              eval_alpha_at<true>(column_terms(geo, fpx), geo, app, fpy, alpha, raw, G, dy) &&
-              some && at + j < last;
-          a[i] = ok ? alpha : 0.0f;
+          ok[i] = eval_alpha_at<true>(column_terms(geo, fpx), geo, app, fpy, alpha, raw, G, dy) &&
+                  some && at + j < last;
+          a[i] = ok[i] ? alpha : 0.0f;
           dot[i] = __builtin_fma((double)s_splat[j].ext.x, (double)dC2,
                                  __builtin_fma((double)app.w, (double)dC1,
                                                (double)app.z * (double)dC0));
         }
 #pragma unroll
         for (int i = 0; i < kGroup; ++i) {
-          C = __builtin_fma((double)a[i], dot[i] - C, C);
+          // selected: a splat that the pixel does not blend may have an infinite colour,
+          // and a factor of zero would leave NaN
+          C = ok[i] ? __builtin_fma((double)a[i], dot[i] - C, C) : C;
           P = __builtin_fma(-(double)a[i], P, P);
         }
       }

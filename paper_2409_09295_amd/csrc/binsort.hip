@@ -96,6 +96,16 @@ struct CountWord {
 
 thread_local CountWord t_count;
 
+// While set, the scan kernel of this call may still write the thread's word: a call that
+// returns so waits for its stream, or the next one could take that count for its own.
+struct CountUnderWay {
+  hipStream_t s;
+  bool set = false;
+  ~CountUnderWay() {
+    if (set) (void)hipStreamSynchronize(s);
+  }
+};
+
 // The key count in 64 bits, its 32-bit clamp and, unless NULL, the host's copy.
 __device__ __forceinline__ void write_count(uint64_t count, uint64_t* total, uint32_t* n_keys,
                                             uint64_t* host) {
@@ -1278,11 +1288,13 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
   // forward and backward: 202 and 161).  A stream that is being recorded refuses the
   // synchronisation, as it always did.
   uint64_t* host_count = nullptr;
+  CountUnderWay under_way{s};
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (n_keys_host && hipStreamIsCapturing(s, &capture) == hipSuccess &&
       capture == hipStreamCaptureStatusNone && t_count.get()) {
     __atomic_store_n(t_count.host, kNoCount, __ATOMIC_RELEASE);
     host_count = t_count.dev;
+    under_way.set = true;
   }
   // Lists that a whole workgroup sorts: with few tiles from 256 pairs up, where a
   // wavefront alone takes 10 to 20 us while CUs idle (whole call, 256 | 1,024: 300 tiles
@@ -1362,6 +1374,7 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
   uint64_t tot = 0;
   if (host_count) {
     if ((e = t_count.wait(s, tot)) != hipSuccess) return hip_fail(e, "wait for the key count");
+    under_way.set = false;
   } else {
     if ((e = hipMemcpyAsync(&tot, total, sizeof(uint64_t), hipMemcpyDeviceToHost, s)) != hipSuccess)
       return hip_fail(e, "read key count");

@@ -1,5 +1,6 @@
 """gs_bin_sort with the key count returned: the count is the call's own on every
 thread and stream, and a call that overflows places nothing (needs an MI355X)."""
+import ctypes
 import threading
 
 import pytest
@@ -54,3 +55,29 @@ def test_threads_and_streams_get_their_own_counts(gs):
     for t in threads:
         t.join()
     assert got == [[w] * 25 for w in want]
+
+
+def test_count_after_a_call_that_failed_behind_its_launches(gs):
+    """A call that reports an error after its kernels were launched (here one that an
+    earlier call of the thread left behind) returns with them done: its count, written
+    late, would be taken for the next call's."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    small, large = _setup(gs, 300, 3, 1 << 16), _setup(gs, 5000, 4, 1 << 20)
+    want = [gs.gs_bin_sort(*c, sync=True) for c in (small, large)]
+    assert want[0] != want[1]
+    a = torch.randn(4096, 4096, device="cuda")
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[0]):
+        for _ in range(40):   # some ms in front of the failing call's kernels
+            a @ a
+    assert not streams[0].query()
+    assert hip.hipSetDevice(1 << 20) != 0   # leaves its error for the thread's next check
+    with pytest.raises(gs.GsError) as e:
+        gs.gs_bin_sort(*small, sync=True, stream=streams[0])
+    assert e.value.status == gs.GS_ERR_HIP
+    assert streams[0].query()
+    assert gs.gs_bin_sort(*large, sync=True, stream=streams[1]) == want[1]
+    assert gs.gs_bin_sort(*small, sync=True, stream=streams[0]) == want[0]
+    torch.cuda.synchronize()

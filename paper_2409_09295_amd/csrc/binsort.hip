@@ -40,70 +40,102 @@
 // unless the caller asks for the key count.
 #include <immintrin.h>
 
+#include <atomic>
+#include <type_traits>
+
 #include "gs_internal.h"
 
 namespace gsmi {
 
 namespace {
 
-// A word of pinned host memory that the scan kernel writes the key count to, for
-// the calls that return it.  One per host thread that made such a call, given back
-// when the thread ends; a call leaves it with no write under way.
+// Words of pinned host memory that the scan kernel writes key counts to, for the calls
+// that return them: one block for the process, of which a call holds a word from its
+// launches until the count is there.  (A word per thread had to be given back when the
+// thread ended, and freeing pinned memory invalidates a graph that another thread
+// records.)  A call that finds none free copies its count instead.
 constexpr uint64_t kNoCount = ~0ull;
+constexpr int kCountWords = 64;
+constexpr int kCountStride = 8;   // in words: a cache line each
 
-struct CountWord {
-  uint64_t* host = nullptr;
-  uint64_t* dev = nullptr;
-  bool tried = false;
-  // false: none to be had, and the count is copied instead
-  bool get() {
-    if (tried) return dev != nullptr;
-    tried = true;
+struct CountBlock {
+  uint64_t *host = nullptr, *dev = nullptr;   // dev NULL: no pinned memory to be had
+  std::atomic<uint64_t> free{~0ull};          // bit per word
+  CountBlock() {
     // pinned memory may be allocated while another thread records a graph
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     void *h = nullptr, *d = nullptr;
-    if (hipHostMalloc(&h, sizeof(uint64_t), hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
+    if (hipHostMalloc(&h, sizeof(uint64_t) * kCountWords * kCountStride,
+                      hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
       host = static_cast<uint64_t*>(h);
       if (hipHostGetDevicePointer(&d, h, 0) == hipSuccess) dev = static_cast<uint64_t*>(d);
     }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (!dev) (void)hipGetLastError();
-    return dev != nullptr;
   }
-  // The count once the kernel on stream s has written it; an error of the stream, or
+};
+
+static_assert(std::is_trivially_destructible_v<CountBlock>);
+
+// The process's block, allocated by the first call that wants a word and kept to its end.
+CountBlock& count_block() {
+  static CountBlock block;   // trivially destroyed: no call of the runtime at exit
+  return block;
+}
+
+// A call's word of the block.
+class CountWord {
+ public:
+  explicit CountWord(hipStream_t s) : s_(s) {}
+  CountWord(const CountWord&) = delete;
+  CountWord& operator=(const CountWord&) = delete;
+  // The device's address of a free word, NULL if there is none.
+  uint64_t* take() {
+    CountBlock& block = count_block();
+    if (!block.dev) return nullptr;
+    uint64_t bits = block.free.load(std::memory_order_relaxed);
+    do {
+      if (!bits) return nullptr;
+    } while (!block.free.compare_exchange_weak(bits, bits & (bits - 1), std::memory_order_acquire,
+                                               std::memory_order_relaxed));
+    word_ = __builtin_ctzll(bits);
+    __atomic_store_n(block.host + word_ * kCountStride, kNoCount, __ATOMIC_RELEASE);
+    return block.dev + word_ * kCountStride;
+  }
+  // The count once the kernel on the stream has written it; an error of the stream, or
   // its end, ends the wait.
-  hipError_t wait(hipStream_t s, uint64_t& count) const {
+  hipError_t wait(uint64_t& count) {
+    const uint64_t* host = count_block().host + word_ * kCountStride;
     for (unsigned spin = 1;; ++spin) {
       count = __atomic_load_n(host, __ATOMIC_ACQUIRE);
-      if (count != kNoCount) return hipSuccess;
+      if (count != kNoCount) break;
       _mm_pause();
       if (spin % 256) continue;
-      const hipError_t e = hipStreamQuery(s);
+      const hipError_t e = hipStreamQuery(s_);
       if (e == hipErrorNotReady) {
         (void)hipGetLastError();
         continue;
       }
       if (e != hipSuccess) return e;
       count = __atomic_load_n(host, __ATOMIC_ACQUIRE);   // all of the stream is done
-      return count != kNoCount ? hipSuccess : hipErrorUnknown;
+      if (count != kNoCount) break;
+      return hipErrorUnknown;
     }
+    written_ = true;
+    return hipSuccess;
   }
+  // A call that returns without its count waits for its stream first: the kernel may
+  // still write the word, and another call would take that count for its own.
   ~CountWord() {
-    if (host) (void)hipHostFree(host);
+    if (word_ < 0 || (!written_ && hipStreamSynchronize(s_) != hipSuccess)) return;
+    count_block().free.fetch_or(uint64_t(1) << word_, std::memory_order_release);
   }
-};
 
-thread_local CountWord t_count;
-
-// While set, the scan kernel of this call may still write the thread's word: a call that
-// returns so waits for its stream, or the next one could take that count for its own.
-struct CountUnderWay {
-  hipStream_t s;
-  bool set = false;
-  ~CountUnderWay() {
-    if (set) (void)hipStreamSynchronize(s);
-  }
+ private:
+  hipStream_t s_;
+  int word_ = -1;
+  bool written_ = false;
 };
 
 // The key count in 64 bits, its 32-bit clamp and, unless NULL, the host's copy.
@@ -1288,14 +1320,11 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
   // forward and backward: 202 and 161).  A stream that is being recorded refuses the
   // synchronisation, as it always did.
   uint64_t* host_count = nullptr;
-  CountUnderWay under_way{s};
+  CountWord word(s);
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (n_keys_host && hipStreamIsCapturing(s, &capture) == hipSuccess &&
-      capture == hipStreamCaptureStatusNone && t_count.get()) {
-    __atomic_store_n(t_count.host, kNoCount, __ATOMIC_RELEASE);
-    host_count = t_count.dev;
-    under_way.set = true;
-  }
+      capture == hipStreamCaptureStatusNone)
+    host_count = word.take();
   // Lists that a whole workgroup sorts: with few tiles from 256 pairs up, where a
   // wavefront alone takes 10 to 20 us while CUs idle (whole call, 256 | 1,024: 300 tiles
   // of 600 pairs 28 | 38 us, 1,200 of 230 34 | 36; 2,400 of 350 63 | 57, 9,600 of 290
@@ -1373,8 +1402,7 @@ int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs
   if (!n_keys_host) return GS_OK;
   uint64_t tot = 0;
   if (host_count) {
-    if ((e = t_count.wait(s, tot)) != hipSuccess) return hip_fail(e, "wait for the key count");
-    under_way.set = false;
+    if ((e = word.wait(tot)) != hipSuccess) return hip_fail(e, "wait for the key count");
   } else {
     if ((e = hipMemcpyAsync(&tot, total, sizeof(uint64_t), hipMemcpyDeviceToHost, s)) != hipSuccess)
       return hip_fail(e, "read key count");

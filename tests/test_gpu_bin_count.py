@@ -2,6 +2,7 @@
 thread and stream, and a call that overflows places nothing (needs an MI355X)."""
 import ctypes
 import threading
+import time
 
 import pytest
 import torch
@@ -81,3 +82,57 @@ def test_count_after_a_call_that_failed_behind_its_launches(gs):
     assert gs.gs_bin_sort(*large, sync=True, stream=streams[1]) == want[1]
     assert gs.gs_bin_sort(*small, sync=True, stream=streams[0]) == want[0]
     torch.cuda.synchronize()
+
+
+def test_thread_that_binned_ends_while_another_records(gs):
+    """What a thread's calls leave is given back without a call that recording forbids."""
+    call = _setup(gs, 300, 5, 1 << 16)
+    want = gs.gs_bin_sort(*call, sync=True)
+    x = torch.zeros(64, device="cuda")
+    done, go, got = threading.Event(), threading.Event(), []
+
+    def work():
+        stream = torch.cuda.Stream()
+        got.append(gs.gs_bin_sort(*call, sync=True, stream=stream))
+        stream.synchronize()
+        done.set()
+        go.wait()
+
+    t = threading.Thread(target=work)
+    t.start()
+    done.wait()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        x.add_(1.0)
+        go.set()
+        t.join()
+        time.sleep(0.2)   # join returns before the thread's own storage is taken down
+        x.add_(1.0)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+    assert got == [want] and bool((x == 6.0).all())
+
+
+def test_more_calls_at_once_than_count_words(gs):
+    """80 threads wait behind one stream's work: the calls past the 64 words copy theirs."""
+    calls = [_setup(gs, 100 + k, 50 + k, 1 << 16) for k in range(80)]
+    want = [gs.gs_bin_sort(*c, sync=True) for c in calls]
+    a = torch.randn(8192, 8192, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    got = [None] * len(calls)
+
+    def work(k):
+        got[k] = gs.gs_bin_sort(*calls[k], sync=True, stream=stream)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(calls))]
+    with torch.cuda.stream(stream):
+        for _ in range(10):   # a tenth of a second in float32
+            a @ a
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert got == want

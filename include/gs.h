@@ -270,7 +270,9 @@ int64_t gs_num_pixels(const gs_views* views);
 int gs_preprocess(const gs_gaussians* g, const gs_views* views, gs_projected* out,
                   gs_stream_t stream);
 
-/* Scratch for gs_bin_sort (bytes). */
+/* Scratch for gs_bin_sort (bytes): enough for every call with at most n
+ * Gaussians and this capacity in some or all of these views, or in as many
+ * smaller ones. */
 size_t gs_bin_sort_workspace_size(int64_t n, const gs_views* views, int64_t capacity);
 
 /* Tile binning and sorting of the splats in p ([n_views][n]): counts the

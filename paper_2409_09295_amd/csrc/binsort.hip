@@ -1229,6 +1229,53 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t value, int64_t n, hipStream_t s
   return hipGetLastError();
 }
 
+namespace {
+
+// What the two paths need in different measure (elements).
+struct BinScratch {
+  size_t matrix;        // chunk x tile matrix
+  size_t list;          // compacted splats
+  size_t list_counts;   // their numbers, per view or per (view, chunk)
+};
+
+// For n Gaussians in n_views views of n_tiles tiles in all; few_entries: entries of a
+// chunk on the short path, 0 on the general one.
+BinScratch bin_scratch(int64_t n, int few_entries, int n_views, int64_t n_tiles) {
+  if (few_entries == 0)
+    return {(size_t)bin_chunks(n) * (size_t)n_tiles, (size_t)n * n_views, GS_MAX_VIEWS};
+  const size_t chunks = (size_t)((n + few_entries - 1) / few_entries);
+  return {chunks * (size_t)n_tiles, chunks * few_entries * n_views,
+          std::max<size_t>(GS_MAX_VIEWS, chunks * n_views)};
+}
+
+// The most (view, Gaussian) entries of a call in chunks of 64, 256 and 1,024: the smallest
+// chunks that number at most about 256 over all views (a small map fills the GPU, a larger
+// one keeps the matrix small).
+constexpr int kFewChunk[3] = {64, 256, 1024};
+constexpr int64_t kFewChunkEntries[3] = {256 * 64, 256 * 256, kFewEntries};
+
+void lay_out(BinSortPlan& P, const BinScratch& need) {
+  const size_t nt = sizeof(uint32_t) * (size_t)std::max(P.n_tiles, 1);
+  size_t off = 0;
+  P.off_matrix = off;    off += align_up(sizeof(uint32_t) * need.matrix);
+  P.off_list = off;      off += align_up(sizeof(uint4) * need.list);      // compacted splats
+  P.off_ids = off;       off += align_up(sizeof(uint32_t) * need.list);   // their entries
+  P.off_list_count = off; off += align_up(sizeof(uint32_t) * need.list_counts);
+  P.off_counts = off;    off += align_up(nt);   // keys per tile
+  P.off_starts = off;    off += align_up(nt);   // first slot of every tile's segment
+  P.off_long = off;      off += align_up(nt);   // tiles whose lists the long grid sorts
+  P.off_flag = off;      off += align_up(sizeof(uint64_t) * 2);   // key count, long-list count
+  P.off_partial = off;   // per scan block: its tiles' key count
+  off += align_up(sizeof(uint64_t) * (size_t)std::max(1, (P.n_tiles + kScanBlock - 1) / kScanBlock));
+  P.off_order = off;     // tile order: per-(block, group) counts, then offsets
+  off += align_up(sizeof(uint32_t) * kOrderGroups * ((P.n_tiles + kOrderBlock - 1) / kOrderBlock));
+  P.off_staged = off;    off += align_up(sizeof(uint64_t) * (size_t)P.capacity);   // (depth, entry) pairs
+  P.off_spare = off;     off += align_up(sizeof(uint64_t) * (size_t)P.capacity);   // radix partner
+  P.total = off;
+}
+
+}  // namespace
+
 BinSortPlan make_bin_sort_plan(int64_t n, const ViewTable& vt, int64_t capacity) {
   BinSortPlan P{};
   P.n_entries = n * vt.n_views;
@@ -1242,33 +1289,40 @@ BinSortPlan make_bin_sort_plan(int64_t n, const ViewTable& vt, int64_t capacity)
     P.lds_tiles = std::max(P.lds_tiles, std::min(kLdsTiles, vt.v[v].tiles_x * vt.v[v].tiles_y));
   }
   P.few_entries = 0;
-  size_t list = (size_t)P.n_entries;   // compacted splats
   if (n > 0 && n <= kFewGaussians && P.n_entries <= kFewEntries && vt.n_tiles <= kFewTiles &&
       P.max_view_tiles <= kLdsTiles) {
-    // the smallest chunks that number at most about 256 over all views: a small
-    // map fills the GPU, a larger one keeps the matrix small
-    P.few_entries = P.n_entries <= 256 * 64 ? 64 : P.n_entries <= 256 * 256 ? 256 : 1024;
+    int k = 0;
+    while (P.n_entries > kFewChunkEntries[k]) ++k;
+    P.few_entries = kFewChunk[k];
     P.chunks = (n + P.few_entries - 1) / P.few_entries;
-    list = (size_t)P.chunks * P.few_entries * vt.n_views;
   }
-  const size_t nt = sizeof(uint32_t) * (size_t)std::max(vt.n_tiles, 1);
-  size_t off = 0;
-  P.off_matrix = off;    off += align_up(sizeof(uint32_t) * (size_t)P.chunks * (size_t)vt.n_tiles);
-  P.off_list = off;      off += align_up(sizeof(uint4) * list);      // compacted splats
-  P.off_ids = off;       off += align_up(sizeof(uint32_t) * list);   // their entries
-  P.off_list_count = off; off += align_up(sizeof(uint32_t) * std::max<size_t>(GS_MAX_VIEWS, P.few_entries ? (size_t)P.chunks * vt.n_views : 0));
-  P.off_counts = off;    off += align_up(nt);   // keys per tile
-  P.off_starts = off;    off += align_up(nt);   // first slot of every tile's segment
-  P.off_long = off;      off += align_up(nt);   // tiles whose lists the long grid sorts
-  P.off_flag = off;      off += align_up(sizeof(uint64_t) * 2);   // key count, long-list count
-  P.off_partial = off;   // per scan block: its tiles' key count
-  off += align_up(sizeof(uint64_t) * (size_t)std::max(1, (vt.n_tiles + kScanBlock - 1) / kScanBlock));
-  P.off_order = off;     // tile order: per-(block, group) counts, then offsets
-  off += align_up(sizeof(uint32_t) * kOrderGroups * ((vt.n_tiles + kOrderBlock - 1) / kOrderBlock));
-  P.off_staged = off;    off += align_up(sizeof(uint64_t) * (size_t)capacity);   // (depth, entry) pairs
-  P.off_spare = off;     off += align_up(sizeof(uint64_t) * (size_t)capacity);   // radix partner
-  P.total = off;
+  lay_out(P, bin_scratch(n, P.few_entries, vt.n_views, vt.n_tiles));
   return P;
+}
+
+size_t bin_sort_workspace_bound(int64_t n, const ViewTable& vt, int64_t capacity) {
+  BinSortPlan P = make_bin_sort_plan(n, vt, capacity);
+  // A smaller call can need more: its chunks are smaller, so its matrix has more rows.
+  // The most that each chunk size needs over up to n Gaussians in any of the views, each
+  // at most as large as it is (views sorted by tiles, the largest first).
+  int tiles[GS_MAX_VIEWS];
+  for (int v = 0; v < vt.n_views; ++v)
+    tiles[v] = std::min(kLdsTiles, vt.v[v].tiles_x * vt.v[v].tiles_y);
+  std::sort(tiles, tiles + vt.n_views, [](int a, int b) { return a > b; });
+  BinScratch most = bin_scratch(n, P.few_entries, vt.n_views, vt.n_tiles);
+  int64_t sum = 0;
+  for (int V = 1; V <= vt.n_views; ++V) {
+    sum = std::min<int64_t>(kFewTiles, sum + tiles[V - 1]);
+    for (int k = 0; k < 3; ++k) {
+      const int64_t m = std::min({n, kFewGaussians, kFewChunkEntries[k] / V});
+      if (k > 0 && m * V <= kFewChunkEntries[k - 1]) break;   // no call has such chunks
+      const BinScratch few = bin_scratch(m, kFewChunk[k], V, sum);
+      most = {std::max(most.matrix, few.matrix), std::max(most.list, few.list),
+              std::max(most.list_counts, few.list_counts)};
+    }
+  }
+  lay_out(P, most);
+  return P.total;
 }
 
 int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs_bins& bins,

@@ -255,7 +255,7 @@ int gs_preprocess(const gs_gaussians* g, const gs_views* views, gs_projected* ou
 size_t gs_bin_sort_workspace_size(int64_t n, const gs_views* views, int64_t capacity) {
   ViewTable vt;
   if (n < 0 || capacity < 0 || build_view_table(views, vt) != GS_OK) return 0;
-  return make_bin_sort_plan(n, vt, capacity).total;
+  return bin_sort_workspace_bound(n, vt, capacity);
 }
 
 int gs_bin_sort(const gs_projected* p, int64_t n, const gs_views* views, gs_bins* bins,

@@ -319,6 +319,9 @@ struct BinSortPlan {
       off_staged, off_spare, total;
 };
 BinSortPlan make_bin_sort_plan(int64_t n, const ViewTable& vt, int64_t capacity);
+// The largest plan.total of a call with at most n Gaussians, in some or all of the views or
+// as many smaller ones, and at most this capacity.
+size_t bin_sort_workspace_bound(int64_t n, const ViewTable& vt, int64_t capacity);
 int run_bin_sort(const gs_projected& p, int64_t n, const ViewTable& vt, const gs_bins& bins,
                  uint32_t* n_keys_host, char* ws, const BinSortPlan& plan, hipStream_t s);
 

@@ -624,14 +624,22 @@ __device__ __forceinline__ int wg_piece(int p, int c) {
 // Fragment: this lane's channel (of the 16 at the address) at pixels 4 g .. 4 g
 // + 3 and 16 + 4 g .. of a 32-pixel row, g = lane / 16; dz and the input use
 // the same order of pixels.
-__device__ __forceinline__ bf16x8 wg_fragment(const char* p) {
+__device__ __forceinline__ bf16x8 wg_fragment(const char* p, const char* p16) {
   using lds = __attribute__((address_space(3))) short4v*;
   const short4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)p);
-  const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)(p + 16 * 64));
+  const short4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds)p16);
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
+__device__ __forceinline__ bf16x8 wg_fragment(const char* p) { return wg_fragment(p, p + 16 * 64); }
 
-template <int NCO, int NCI, int NR>
+// EDGE: a strip or a step may reach beyond the image, whose last rows in a wavefront's
+// four are REM = H % 4. dz is zero there, but the taps that look back pair its first
+// column and row beside the image with the input's last, and zero times an infinite
+// input is NaN in a sum that has no such term. So the column's address moves on by one
+// pixel (zero) and the row's fragment is cleared. Images of whole strips and steps need
+// neither and go without: 160x121 of 32 -> 32 channels takes 13.4 us instead of 13.3,
+// 242x186 of 256 -> 256 79.5 instead of 77.3.
+template <int NCO, int NCI, int NR, bool EDGE, int REM>
 __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_strip_kernel(
     ActView x1, ActView x2, ActView dz, ActView mask, int N, int H, int W, int cout, int cin,
     int n_pairs, int ci_groups, int steps_per_wg, float* __restrict__ dw,
@@ -717,11 +725,21 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
   const int px = 4 * (lane >> 4) + ((lane >> 2) & 3), ch = (lane & 3) * 8;
   const char* a_base[2];
   const char* b_base[2];
+  const char* b_base16[2];   // of the fragment's second half
+  auto set_b = [&](int cols) {   // columns of the image from the strip's first on
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+    for (int h = 0; h < 2; ++h) {
+      const char* group = s_x + ciw * XGROUP + ch;
+      const bool back = EDGE && dx == 0;
+      b_base[h] = group + wg_piece(px + dx + (back && px == cols ? 1 : 0), 2 * h);
+      b_base16[h] = EDGE ? group + wg_piece(px + 16 + dx + (back && px + 16 == cols ? 1 : 0), 2 * h)
+                         : b_base[h] + 16 * 64;
+    }
+  };
+  if constexpr (!EDGE) set_b(0);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
     a_base[h] = s_z + cow * ZGROUP + rw * 4 * WG_ZROW + wg_piece(px, 2 * h) + ch;
-    b_base[h] = s_x + ciw * XGROUP + wg_piece(px + dx, 2 * h) + ch;
-  }
   const bool do_bias = dbias != nullptr && ci0 == 0 && ciw == 0 && dx == 1;   // wavefront-uniform
   f32x4 acc[3][2][2], bacc[2];
 #pragma unroll
@@ -741,6 +759,7 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
   bool start = true;   // the first step of the run or of a strip
   for (int k = k_beg, zbuf = 0; k < k_end; ++k, zbuf ^= 1) {
     if (start) {   // rows r0 - 1 and r0 as well
+      if constexpr (EDGE) set_b(W - tx0);
       __syncthreads();   // the previous strip's fragments have been read
 #pragma unroll
       for (int u = 0; u < HIT; ++u) {
@@ -763,6 +782,7 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
       if (p < SR * WG_XW) *reinterpret_cast<uint4*>(x_place(p, first + 2)) = rx[u];
     }
     __syncthreads();
+    const int rows = H - r0 - 4 * rw;   // of dz in the image, from the wavefront's first
     if (k + 1 < k_end) {
       locate(k + 1);
       start = r0 == 0;
@@ -781,11 +801,18 @@ __global__ __launch_bounds__(64 * 3 * NCO * NCI * NR, 3) void conv3x3_wgrad_stri
       if (at >= RING) at -= RING;
       bf16x8 b[2];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) b[h] = wg_fragment(b_base[h] + at * WG_XROW);
+      for (int h = 0; h < 2; ++h) b[h] = wg_fragment(b_base[h] + at * WG_XROW, b_base16[h] + at * WG_XROW);
 #pragma unroll
-      for (int dy = 0; dy < 3; ++dy) {
+      for (int dy = 2; dy >= 0; --dy) {
         const int i = j - dy;
         if (i < 0 || i >= 4) continue;
+        if (EDGE && dy == 0 && j == REM && (REM > 0 || NR > 1)) {
+          typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
+          const uint32_t keep = rows == REM ? 0u : ~0u;
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            b[h] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(uint4v, b[h]) & keep);
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1551,13 +1578,23 @@ hipError_t nn_conv3x3_wgrad(const gs_act* x1, const gs_act* x2, const gs_act* dz
     const int per = (steps + runs_wanted - 1) / runs_wanted;
     const int runs = (steps + per - 1) / per;
     const unsigned grid = (unsigned)((runs * (int64_t)pairs + 7) / 8 * 8);
+#define GS_WGRAD_EDGE(O, I, R, E, M)                                                            \
+  hipLaunchKernelGGL((conv3x3_wgrad_strip_kernel<O, I, R, E, M>), dim3(grid),                   \
+                     dim3(64 * 3 * O * I * R), 0, s, view(x1), view(x2), view(dz), view(mask),  \
+                     x1->n, x1->h, x1->w, cout, cin, pairs, ci_groups, per, dw, dbias)
 #define GS_WGRAD(O, I, R)                                                                       \
-  hipLaunchKernelGGL((conv3x3_wgrad_strip_kernel<O, I, R>), dim3(grid), dim3(64 * 3 * O * I * R), 0, \
-                     s, view(x1), view(x2), view(dz), view(mask), x1->n, x1->h, x1->w, cout, cin, \
-                     pairs, ci_groups, per, dw, dbias)
+  do {                                                                                          \
+    const int rem = x1->h % 4;                                                                  \
+    if (x1->w % WG_W == 0 && x1->h % rows == 0) GS_WGRAD_EDGE(O, I, R, false, 0);               \
+    else if (rem == 0) GS_WGRAD_EDGE(O, I, R, true, 0);                                         \
+    else if (rem == 1) GS_WGRAD_EDGE(O, I, R, true, 1);                                         \
+    else if (rem == 2) GS_WGRAD_EDGE(O, I, R, true, 2);                                         \
+    else GS_WGRAD_EDGE(O, I, R, true, 3);                                                       \
+  } while (0)
     if (one_co) GS_WGRAD(1, 1, 2);
     else if (one_ci) GS_WGRAD(2, 1, 1);
     else GS_WGRAD(2, 2, 1);
+#undef GS_WGRAD_EDGE
 #undef GS_WGRAD
     return hipGetLastError();
   }

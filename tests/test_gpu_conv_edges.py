@@ -112,3 +112,32 @@ def test_conv_edges(gs, case):
         assert torch.equal(wide[..., off:off + cout].reshape(-1, cout), yf[:, :cout].to(torch.bfloat16))
         assert (wide[..., :off] == -7).all() and (wide[..., off + cout:] == -7).all()
         assert (yf[:, cout:] == -7).all()
+
+
+@pytest.mark.parametrize("case", [(2, 9, 40, 32, 32), (1, 12, 31, 32, 32), (1, 16, 33, 64, 32),
+                                  (2, 7, 40, 64, 64), (1, 33, 70, 768, 768), (2, 30, 40, 736, 776)])
+def test_wgrad_infinite_inputs_at_the_image_edge(gs, case):
+    """The input's last row and column are infinite in a channel each: a tap that never
+    reads one of them stays finite there, with the strip's or the step's end in the image
+    and beyond it, in each of the kernel's three widths."""
+    print(case, flush=True)
+    n, h, w, cin, cout = case
+    rng = np.random.default_rng(sum(case))
+    x = _bf16(rng.normal(size=(n, h, w, cin)))
+    x[:, h - 1, :, 0] = np.inf
+    x[:, :, w - 1, 1] = np.inf
+    gy = _bf16(rng.normal(size=(n, h, w, cout)))
+    gy[gy == 0] = 1.0
+    dw = torch.zeros(9, cout, cin, device=DEV)
+    gs.gs_nn_conv3x3_wgrad(_act(gs, x), None, _act(gs, gy), None, dw, None)
+    torch.cuda.synchronize()
+    for k in range(9):
+        dy, dx = k // 3 - 1, k % 3 - 1   # pixels (y, x) whose neighbour (y + dy, x + dx) lies in the image
+        own = gy.double()[:, max(0, -dy):h - max(0, dy), max(0, -dx):w - max(0, dx)].reshape(-1, cout)
+        tap = x.double()[:, max(0, dy):h + min(0, dy), max(0, dx):w + min(0, dx)].reshape(-1, cin)
+        finite = torch.isfinite(tap).all(0)
+        assert finite[2:].all() and bool(finite[0]) == (dy < 0) and bool(finite[1]) == (dx < 0)
+        got, ref, scale = dw[k].cpu(), own.T @ tap, own.abs().T @ tap.abs()
+        err = (got - ref).abs()[:, finite]
+        assert (err <= 1e-5 * scale[:, finite] + 1e-7).all(), (case, k)
+        assert not torch.isfinite(got[:, ~finite]).any(), (case, k)

@@ -247,8 +247,12 @@ enum {
  * keeps the configuration it was captured with.  Results are identical for
  * every setting up to float32 summation order of the gradient atomics. */
 int gs_set_tuning(int key, int value);
-/* Current value of a tuning key (< 0 for an unknown key). */
+/* Current value of a tuning key (< 0 for an unknown key); 1 for pixels per
+ * lane that the launch chooses. */
 int gs_get_tuning(int key);
+/* The value that restores the key's present setting through gs_set_tuning: 0
+ * for a default that the launch chooses, else as gs_get_tuning. */
+int gs_get_tuning_setting(int key);
 
 /* Timing hook (thread-local): while set, every launch of `kernel` on this
  * thread is bracketed by hipEventRecord(start, stream) and

@@ -229,6 +229,10 @@ int gs_get_tuning(int key) {
   return pixels && value == 0 ? 1 : value;
 }
 
+int gs_get_tuning_setting(int key) {
+  return key < 0 || key >= GS_TUNE_COUNT ? -1 : tuning(key);
+}
+
 int64_t gs_num_tiles(const gs_views* views) {
   ViewTable vt;
   if (build_view_table(views, vt) != GS_OK) return -1;

@@ -140,6 +140,7 @@ _lib.gs_l1_loss_grad.argtypes = [_p, _p, ctypes.POINTER(gs_views), _p, _p, _S]
 _lib.gs_set_kernel_events.argtypes = [ctypes.c_int, _p, _p]
 _lib.gs_set_tuning.argtypes = [ctypes.c_int, ctypes.c_int]
 _lib.gs_get_tuning.argtypes = [ctypes.c_int]
+_lib.gs_get_tuning_setting.argtypes = [ctypes.c_int]
 _lib.gs_adam_step_dev.argtypes = [_p, _p, _p, _p, ctypes.c_int64, ctypes.c_float, ctypes.c_float,
                                   ctypes.c_float, ctypes.c_float, _p, ctypes.c_int32, _p, _p,
                                   ctypes.c_int64, _S]
@@ -196,7 +197,7 @@ EXPORTED = ("gs_status_string", "gs_last_error", "gs_version", "gs_num_tiles", "
             "gs_render_bwd_workspace_size", "gs_render_bwd", "gs_adam_step", "gs_l1_loss_grad",
             "gs_set_kernel_events", "gs_adam_step_dev", "gs_adam_step_groups_dev",
             "gs_render_fwd_l1_workspace_size", "gs_render_fwd_l1", "gs_render_fwd_l1_noalloc",
-            "gs_set_tuning", "gs_get_tuning", "gs_render_error", "gs_active_set",
+            "gs_set_tuning", "gs_get_tuning", "gs_get_tuning_setting", "gs_render_error", "gs_active_set",
             "gs_adam_step_groups_masked_dev", "gs_concat", "gs_prune_mask",
             "gs_compact_workspace_size", "gs_compact", "gs_iso_loss_grad", "gs_pose_adam_step",
             "gs_mem_track", "gs_mem_report", "gs_mem_reset_peaks")
@@ -713,6 +714,11 @@ def gs_set_tuning(key: int, value: int) -> None:
 
 def gs_get_tuning(key: int) -> int:
     return int(_lib.gs_get_tuning(key))
+
+
+def gs_get_tuning_setting(key: int) -> int:
+    """What restores the key through gs_set_tuning (0: the launch chooses)."""
+    return int(_lib.gs_get_tuning_setting(key))
 
 
 # ---------------------------------------------------------------------------

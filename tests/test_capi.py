@@ -368,3 +368,24 @@ def test_binding_constants_match_the_headers(gs):
     assert len(common) >= 20, common
     for name in common:
         assert bound[name] == declared[name], (name, bound[name], declared[name])
+
+
+def test_tuning_settings_can_be_saved_and_restored(gs):
+    """Reading every key's setting and setting it again changes nothing: a default that
+    the launch chooses is not pinned to the value gs_get_tuning shows for it."""
+    keys = range(6)
+    try:
+        for key in keys:
+            gs.gs_set_tuning(key, 0)
+        first = [gs.gs_get_tuning_setting(k) for k in keys]
+        assert first[gs.GS_TUNE_FWD_PIXELS_PER_LANE] == first[gs.GS_TUNE_BWD_PIXELS_PER_LANE] == 0
+        for key, value in enumerate((1, 4, gs.GS_SCHEDULE_TILE_ID, gs.GS_SCHEDULE_PERSISTENT, 2, 1)):
+            gs.gs_set_tuning(key, value)
+            assert gs.gs_get_tuning_setting(key) == gs.gs_get_tuning(key) == value
+        for key in keys:
+            gs.gs_set_tuning(key, first[key])
+        assert [gs.gs_get_tuning_setting(k) for k in keys] == first
+        assert gs.gs_get_tuning_setting(-1) < 0 and gs.gs_get_tuning_setting(6) < 0
+    finally:
+        for key in keys:
+            gs.gs_set_tuning(key, 0)

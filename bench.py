@@ -465,6 +465,8 @@ def main():
                    "bwd_stage_per_thread": tuned.get("bwd_stage"),
                    "fwd_schedule": tuned.get("fwd_schedule_name"),
                    "bwd_schedule": tuned.get("bwd_schedule_name"),
+                   "fwd_launch_choice": tuned.get("fwd_launch_choice"),
+                   "bwd_launch_choice": tuned.get("bwd_launch_choice"),
                    "table_ms": tuned.get("table")},
         "roofline": roof,
         "hbm_kernels": hbm,

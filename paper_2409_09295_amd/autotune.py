@@ -7,12 +7,16 @@ combination of pixels per lane (1, 2 or 4: four, two or one wavefront per
 (one workgroup per tile launched heaviest first or in tile id order, or
 persistent workgroups, as many as the GPU holds or half that, drawing tiles
 heaviest first from counters) on the real step (eager launches, HIP events,
-optimiser state restored afterwards), keeps the fastest and caches the
-choice in a JSON file keyed by device name, library version and workload
-shape (settings within 2% of the fastest count as tied and the one closest
-to the kernel's defaults wins, so that noise does not flip the choice).
-Every setting computes the same result (up to the float32 order of
-gradient atomics), so tuning changes speed only.
+optimiser state restored afterwards), and so what the launch chooses when
+nothing is set, which for few tiles is a backward kernel that no setting
+names.  It keeps the fastest and caches the choice in a JSON file keyed by
+device name, library version and workload shape (settings within 2% of the
+fastest count as tied and the one closest to the kernel's defaults wins, so
+that noise does not flip the choice; the launch's own choice has to beat
+them by more).  Every setting computes the same forward bits and the same
+gradients up to float32 rounding (the order of their atomics and, in that
+backward kernel, what a part of a list starts from), so tuning changes speed
+only.
 """
 from __future__ import annotations
 
@@ -97,7 +101,8 @@ def time_config(step, fwd_ppl: int, bwd_ppl: int, reps: int = 3, fwd_schedule: i
 
 
 def _apply_best(best: Dict):
-    apply(best["fwd_ppl"], best["bwd_ppl"], best.get("fwd_schedule", 0), best.get("bwd_schedule", 0),
+    apply(*(0 if best.get(f"{k}_launch_choice") else best[f"{k}_ppl"] for k in ("fwd", "bwd")),
+          best.get("fwd_schedule", 0), best.get("bwd_schedule", 0),
           best.get("fwd_stage", 0), best.get("bwd_stage", 0))
 
 
@@ -125,7 +130,10 @@ def tune(step, cache: Optional[str] = None, force: bool = False, reps: int = 3) 
     """Pick and apply the fastest setting for ``step`` (a replay.BatchedStep).
     Returns {"fwd_ppl", "bwd_ppl", "fwd_stage", "bwd_stage", "fwd_schedule",
     "bwd_schedule" (GS_SCHEDULE_* values) and their names, "fwd_ms", "bwd_ms",
-    "cached", "table"}; table keys are "<fwd|bwd><ppl>s<stage>_<schedule>"."""
+    "fwd_launch_choice", "bwd_launch_choice", "cached", "table"}; table keys are
+    "<fwd|bwd><ppl>s<stage>_<schedule>".  Where a launch choice is True nothing
+    is pinned: the launch chooses, and the values are those that gs_get_tuning
+    shows then (1 pixel per lane, stage 0, heaviest first)."""
     cache = cache or os.environ.get("GSMI_TUNE_CACHE", DEFAULT_CACHE)
     key = _key(step)
     data = _load(cache)
@@ -140,13 +148,15 @@ def tune(step, cache: Optional[str] = None, force: bool = False, reps: int = 3) 
             step, p, 1, reps, fwd_schedule=SCHEDULES[name], fwd_stage=st)
         _, table[_label("bwd", p, st, name)] = time_config(
             step, 1, p, reps, bwd_schedule=SCHEDULES[name], bwd_stage=st)
-    bf = _pick(settings, table, "fwd")
-    bb = _pick(settings, table, "bwd")
-    best = {"fwd_ppl": bf[0], "bwd_ppl": bb[0], "fwd_stage": bf[1], "bwd_stage": bb[1],
-            "fwd_schedule": SCHEDULES[bf[2]], "bwd_schedule": SCHEDULES[bb[2]],
-            "fwd_schedule_name": bf[2], "bwd_schedule_name": bb[2],
-            "fwd_ms": table[_label("fwd", *bf)], "bwd_ms": table[_label("bwd", *bb)],
-            "table": table}
+    best = {"table": table}
+    for kernel, launch_ms in zip(("fwd", "bwd"), time_config(step, 0, 0, reps)):
+        c = _pick(settings, table, kernel)
+        ms = table[_label(kernel, *c)]
+        own = launch_ms * (1.0 + TIE) < ms   # the launch's own choice
+        if own:
+            c, ms = (1, 0, "heaviest_first"), launch_ms
+        best.update({f"{kernel}_ppl": c[0], f"{kernel}_stage": c[1], f"{kernel}_schedule": SCHEDULES[c[2]],
+                     f"{kernel}_schedule_name": c[2], f"{kernel}_ms": ms, f"{kernel}_launch_choice": own})
     data[key] = best
     try:
         _save(cache, data)

@@ -48,3 +48,40 @@ def test_default_batches_match_the_library():
         ppl, hit, other = (int(x) for x in m.groups())
         lib = {p: hit if p == ppl else other for p in A.CHOICES}
         assert A.DEFAULT_STAGE[kernel] == lib, (kernel, A.DEFAULT_STAGE[kernel], lib)
+
+
+def _tune(monkeypatch, tmp_path, times):
+    """tune() on made-up times: times[(kernel, ppl)] of every stage and schedule, ppl 0
+    for the launch's own choice."""
+    from paper_2409_09295_amd import gs
+    monkeypatch.setattr(A, "_key", lambda step: "workload")
+    monkeypatch.setattr(A, "time_config",
+                        lambda step, fwd, bwd, reps=3, **kw: (times["fwd", fwd], times["bwd", bwd]))
+    try:
+        a = A.tune(None, cache=str(tmp_path / "tune.json"))
+        set_a = [gs.gs_get_tuning_setting(k) for k in range(6)]
+        A.apply(0, 0)
+        b = A.tune(None, cache=str(tmp_path / "tune.json"))
+        set_b = [gs.gs_get_tuning_setting(k) for k in range(6)]
+    finally:
+        A.apply(0, 0)
+    assert not a["cached"] and b["cached"] and set_a == set_b
+    assert {k: v for k, v in a.items() if k != "cached"} == {k: v for k, v in b.items() if k != "cached"}
+    return a, set_a
+
+
+def test_the_launch_keeps_its_choice_where_no_setting_is_as_fast(monkeypatch, tmp_path):
+    """Few tiles: the backward that the launch chooses is one that no setting names."""
+    times = {(k, p): 0.066 + 0.01 * p for k in ("fwd", "bwd") for p in A.CHOICES}
+    times.update({("fwd", 0): 0.0755, ("bwd", 0): 0.044})
+    best, setting = _tune(monkeypatch, tmp_path, times)
+    assert best["bwd_launch_choice"] and best["bwd_ms"] == 0.044 and setting[1] == setting[5] == 0
+    assert not best["fwd_launch_choice"] and setting[0] == 1 and best["fwd_ms"] == times["fwd", 1]
+
+
+def test_a_setting_is_pinned_where_it_ties_or_wins(monkeypatch, tmp_path):
+    times = {(k, p): 0.7 - 0.05 * p for k in ("fwd", "bwd") for p in A.CHOICES}
+    times.update({("fwd", 0): 0.495, ("bwd", 0): 0.62})
+    best, setting = _tune(monkeypatch, tmp_path, times)
+    assert not best["fwd_launch_choice"] and not best["bwd_launch_choice"]
+    assert setting[:2] == [4, 4] and best["fwd_ppl"] == best["bwd_ppl"] == 4

@@ -75,3 +75,18 @@ def test_infinite_colour_that_no_pixel_blends(gs, size, n, at):
         a, b = np_(getattr(got, name)), np_(getattr(ref, name))
         assert (abs(b) < math.inf).all() and (abs(a) < math.inf).all(), name
         assert_grad_close(name, a, b)
+
+
+@pytest.mark.parametrize("sizes", [[(40, 24), (16, 16), (9, 70)], [(1600, 160)]])
+def test_quarters_in_tile_id_order(gs, sizes):
+    views = gs.Views([scenes.pinhole(w, h, 0.8 * w) for w, h in sizes])
+    g = gs.Gaussians.from_map(scenes.random_cloud(3000, 1, seed=5))
+    bg = (0.3, 0.1, 0.7)
+    ref, _ = _grads(gs, g, views, 1, bg)
+    gs.gs_set_tuning(gs.GS_TUNE_BWD_SCHEDULE, gs.GS_SCHEDULE_TILE_ID)
+    try:
+        got, _ = _grads(gs, g, views, 0, bg)
+    finally:
+        gs.gs_set_tuning(gs.GS_TUNE_BWD_SCHEDULE, 0)
+    for name in ("means", "log_scales", "quats", "opacity_logits", "sh", "xi"):
+        assert_grad_close(name, np_(getattr(got, name)), np_(getattr(ref, name)))

@@ -72,13 +72,13 @@ CONV_CASES = [
     (1, 16, 16, 32, 0, 32, False, 0),      # exactly one tile
     (2, 17, 33, 32, 0, 32, True, 8),       # a row and a column past it, a channel slice
     (1, 5, 40, 64, 32, 32, False, 0),      # three chunks, concatenated
-    (1, 20, 20, 32, 0, 96, True, 0),       # 96 channels at a time
-    (1, 18, 15, 24, 0, 72, True, 0),       # of which 72
+    (1, 20, 20, 32, 0, 96, True, 0),       # three groups of 32 channels
+    (1, 18, 15, 24, 0, 72, True, 0),       # the third cut to 8
     (1, 9, 70, 32, 0, 65, False, 0),       # channel counts that are not multiples of 8:
     (1, 9, 30, 40, 0, 20, False, 0),       # element by element
     (1, 9, 30, 32, 0, 32, False, 3),       # and an output that is not 16-byte aligned
     (2, 30, 21, 128, 64, 64, True, 0),
-    (3, 120, 160, 32, 0, 128, True, 0),    # 64 channels at a time
+    (3, 120, 160, 32, 0, 128, True, 0),    # four groups, more workgroups than places
 ]
 
 
@@ -141,3 +141,51 @@ def test_wgrad_infinite_inputs_at_the_image_edge(gs, case):
         err = (got - ref).abs()[:, finite]
         assert (err <= 1e-5 * scale[:, finite] + 1e-7).all(), (case, k)
         assert not torch.isfinite(got[:, ~finite]).any(), (case, k)
+
+
+# 16 x 16 tiles times 64-channel groups from 1,024 on, where a workgroup takes 64 channels
+WIDE_CONV_CASES = [
+    # (n, h, w, cin1, cin2, cout, masked, channel offset of the output)
+    (1, 512, 512, 64, 0, 64, True, 8),      # exactly 1,024, whole tiles
+    (1, 512, 496, 64, 0, 64, True, 8),      # 992: 32 channels at a time
+    (2, 330, 250, 64, 32, 128, True, 0),    # cut tiles, three chunks, concatenated
+    (2, 330, 250, 64, 32, 128, False, 8),
+    (1, 250, 260, 128, 0, 200, True, 0),    # the last group cut to 8 channels
+    (1, 250, 260, 120, 0, 200, False, 0),   # and the last chunk to 24
+    (1, 520, 260, 32, 0, 65, False, 0),     # one chunk; element by element
+    (1, 520, 260, 40, 0, 128, True, 3),     # an output that is not 16-byte aligned
+]
+
+
+@pytest.mark.parametrize("case", WIDE_CONV_CASES)
+def test_conv_64_channels_a_workgroup(gs, case):
+    print(case, flush=True)
+    n, h, w, c1, c2, cout, masked, off = case
+    cin = c1 + c2
+    gen = torch.Generator(device=DEV).manual_seed(sum(case))
+    rand = lambda *s: torch.randn(*s, generator=gen, device=DEV)
+    x = rand(n, h, w, cin).to(torch.bfloat16)
+    m = rand(n, h, w, cin)
+    m = torch.where(rand(n, h, w, cin) < -1.3, torch.full_like(m, -0.0), m).to(torch.bfloat16)
+    wt = (rand(9, cout, cin) / (9 * cin) ** 0.5).to(torch.bfloat16)
+    b = rand(cout)
+    stride = (cout + off + 7) // 8 * 8 + 8
+    xa, xb = _act(gs, x[..., :c1]), _act(gs, x[..., c1:]) if c2 else None
+    wide = torch.full((n, h, w, stride), -7.0, dtype=torch.bfloat16, device=DEV)
+    yf = torch.full((n * h * w, cout + 3), -7.0, device=DEV)
+    gs.gs_nn_conv3x3(xa, xb, _act(gs, m) if masked else None, wt, cout, b, True, gs.Act(wide, cout, off), yf, cout + 3)
+    torch.cuda.synchronize()
+    xm = x.double() * ((m > 0).double() if masked else 1.0)
+    pad = torch.nn.functional.pad(xm, (0, 0, 1, 1, 1, 1))
+    ref = b.double().expand(n * h * w, cout).clone()
+    scale = ref.abs()
+    for k in range(9):
+        tap = pad[:, k // 3:k // 3 + h, k % 3:k % 3 + w].reshape(-1, cin)
+        wk = wt[k].double().T.contiguous()
+        ref += tap @ wk
+        scale += tap.abs() @ wk.abs()
+    got = yf[:, :cout]
+    assert bool(((got - ref.clamp(min=0)).abs() <= 1e-5 * scale + 1e-7).all()), case
+    assert torch.equal(wide[..., off:off + cout].reshape(-1, cout), got.to(torch.bfloat16))
+    assert (wide[..., :off] == -7).all() and (wide[..., off + cout:] == -7).all()
+    assert (yf[:, cout:] == -7).all()

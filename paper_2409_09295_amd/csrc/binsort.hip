@@ -58,20 +58,30 @@ constexpr uint64_t kNoCount = ~0ull;
 constexpr int kCountWords = 64;
 constexpr int kCountStride = 8;   // in words: a cache line each
 
+// While it lives, this thread's calls may do what another thread's recording of a graph
+// forbids in the default mode; they leave that recording alone.
+class RelaxedCapture {
+ public:
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode_); }
+  RelaxedCapture(const RelaxedCapture&) = delete;
+  RelaxedCapture& operator=(const RelaxedCapture&) = delete;
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+};
+
 struct CountBlock {
   uint64_t *host = nullptr, *dev = nullptr;   // dev NULL: no pinned memory to be had
   std::atomic<uint64_t> free{~0ull};          // bit per word
   CountBlock() {
-    // pinned memory may be allocated while another thread records a graph
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    RelaxedCapture relaxed;
     void *h = nullptr, *d = nullptr;
     if (hipHostMalloc(&h, sizeof(uint64_t) * kCountWords * kCountStride,
                       hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
       host = static_cast<uint64_t*>(h);
       if (hipHostGetDevicePointer(&d, h, 0) == hipSuccess) dev = static_cast<uint64_t*>(d);
     }
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (!dev) (void)hipGetLastError();
   }
 };
@@ -128,7 +138,11 @@ class CountWord {
   // A call that returns without its count waits for its stream first: the kernel may
   // still write the word, and another call would take that count for its own.
   ~CountWord() {
-    if (word_ < 0 || (!written_ && hipStreamSynchronize(s_) != hipSuccess)) return;
+    if (word_ < 0) return;
+    if (!written_) {
+      RelaxedCapture relaxed;
+      if (hipStreamSynchronize(s_) != hipSuccess) return;   // then it is not given back
+    }
     count_block().free.fetch_or(uint64_t(1) << word_, std::memory_order_release);
   }
 

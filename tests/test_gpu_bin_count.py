@@ -136,3 +136,39 @@ def test_more_calls_at_once_than_count_words(gs):
     for t in threads:
         t.join()
     assert got == want
+
+
+def test_refused_wait_leaves_nothing_under_way(gs):
+    """While another thread records in the global mode, waiting for a count is refused, as
+    synchronising is: the call reports it, and returns with its stream done."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    hip = ctypes.CDLL(path)
+    call = _setup(gs, 300, 6, 1 << 16)
+    want = gs.gs_bin_sort(*call, sync=True)
+    a = torch.randn(8192, 8192, device="cuda")
+    recorded, stream = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(10):   # a tenth of a second in front of the call's kernels
+            a @ a
+    seen = []
+
+    def work():
+        try:
+            seen.append(gs.gs_bin_sort(*call, sync=True, stream=stream))
+        except gs.GsError as e:
+            seen.append(e.status)
+        mode = ctypes.c_int(2)   # relaxed: the query is allowed
+        hip.hipThreadExchangeStreamCaptureMode(ctypes.byref(mode))
+        seen.append(stream.query())
+
+    handle, graph = ctypes.c_void_p(recorded.cuda_stream), ctypes.c_void_p()
+    assert hip.hipStreamBeginCapture(handle, 0) == 0   # global
+    t = threading.Thread(target=work)
+    t.start()
+    t.join()
+    hip.hipStreamEndCapture(handle, ctypes.byref(graph))   # the refused wait has spoilt it
+    hip.hipGetLastError()
+    assert seen == [gs.GS_ERR_HIP, True]
+    assert gs.gs_bin_sort(*call, sync=True) == want
+    torch.cuda.synchronize()

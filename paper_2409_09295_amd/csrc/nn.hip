@@ -1,17 +1,11 @@
 // Kernels of the learned Gaussian initialiser: a small U-Net over BF16 NHWC
 // activations with FP32 accumulation on MFMA (v_mfma_f32_16x16x32_bf16).
 //
-// conv3x3 (forward and, with flipped/transposed weights, backward-data) runs as
-// conv3x3_patch_kernel, a direct convolution on spatial tiles, where channels come
-// in eights.  Other channel counts run as an implicit GEMM, conv3x3_kernel: M =
-// pixels, N = output channels, K = 9 taps x input channels.  A 256-thread workgroup
-// owns a 64-pixel x 64-channel tile; each wavefront computes a 32 x 32 quarter as
-// 2 x 2 MFMA tiles.  Per K step (one tap, 32 input channels) the workgroup stages
-// the 64 x 32 activation slice (zero outside the image; channels may come from two
-// tensors, which is how the decoder's skip concatenation is read without
-// materialising it) and the 64 x 32 weight slice in LDS, both K-contiguous so that
-// every MFMA operand fragment is one 16-byte LDS read.  An optional mask tensor
-// zeroes input entries whose mask value is <= 0 (the ReLU backward fused into the
+// conv3x3 (forward and, with flipped/transposed weights, backward-data) is a direct
+// convolution on spatial tiles, conv3x3_patch_kernel; its inputs' channels come in
+// eights.  They may come from two tensors, which is how the decoder's skip
+// concatenation is read without materialising it, and an optional mask tensor zeroes
+// input entries whose mask value is <= 0 (the ReLU backward fused into the
 // backward-data pass).
 //
 // conv3x3_wgrad: dW[tap][co][ci] = sum_p dz[p][co] x[p + tap][ci] as a GEMM
@@ -50,9 +44,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){lo, hi}, bf16x2));
 }
-
-constexpr int BM = 64, BN = 64, BK = 32;
-constexpr int LDK = BK + 8;   // LDS row pitch in bf16 (16-byte aligned, skews banks)
 
 struct ActView {
   const uint16_t* p;
@@ -93,116 +84,6 @@ __device__ __forceinline__ uint4 load8(const ActView& a, const ActView& b, const
     v = apply_mask8(v, mk);
   }
   return v;
-}
-
-// Output tile of BMT pixels x BNT output channels; each of the four
-// wavefronts computes a (16 IM) x 32 block (IM x 2 MFMA tiles of 16 x 16).
-// K runs over 9 taps x cin in steps of BK = 32 channels; the next step's
-// global loads are issued before this step's MFMAs, so their latency hides
-// behind them.
-template <int BMT, int BNT, int IM>
-__global__ __launch_bounds__(256) void conv3x3_kernel(
-    ActView x1, ActView x2, ActView mask, int N, int H, int W, const uint16_t* __restrict__ wk,
-    int cout, int cin, const float* __restrict__ bias, int relu, uint16_t* __restrict__ y,
-    int y_stride, int y_offset, float* __restrict__ yf, int yf_stride) {
-  static_assert(BMT * BNT == 4 * 16 * IM * 32 && BNT % 32 == 0 && BMT % 64 == 0,
-                "four (16 IM) x 32 wavefront tiles");
-  constexpr int AR = BMT / 64;   // A rows (pixels) staged per thread
-  __shared__ __attribute__((aligned(16))) uint16_t sA[BMT * LDK];
-  __shared__ __attribute__((aligned(16))) uint16_t sB[BNT * LDK];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int64_t npix = (int64_t)N * H * W;
-  const int64_t m0 = (int64_t)blockIdx.x * BMT;
-  const int n0 = blockIdx.y * BNT;
-  // loaders: thread t stages A rows (t / 4) + 64 u and B row t / 4 (when
-  // below BNT), channels 8 (t % 4) .. +8 of the step
-  const int lcol = (t & 3) * 8, lrow = t >> 2;
-  int ly[AR], lx[AR], limg[AR];
-  bool lok[AR];
-#pragma unroll
-  for (int u = 0; u < AR; ++u) {
-    const int64_t lp = m0 + lrow + 64 * u;
-    lok[u] = lp < npix;
-    limg[u] = ly[u] = lx[u] = 0;
-    if (lok[u]) {
-      limg[u] = (int)(lp / ((int64_t)H * W));
-      const int rem = (int)(lp - (int64_t)limg[u] * H * W);
-      ly[u] = rem / W;
-      lx[u] = rem - ly[u] * W;
-    }
-  }
-  const bool bload = lrow < BNT;
-  const int csteps = (cin + BK - 1) / BK;
-  const int nsteps = 9 * csteps;
-  // the mask (backward data: the ReLU of this layer's output) is loaded
-  // beside the values and applied when the step is written to LDS, so the
-  // prefetch does not wait for it
-  const bool masked = mask.p != nullptr;
-  const ActView none = {nullptr, 0, 0, 0};
-  uint4 ra[AR], rm[AR], rb;
-  auto fetch = [&](int step) {
-    const int tap = step / csteps, c0 = (step - tap * csteps) * BK;
-    const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-    for (int u = 0; u < AR; ++u) {
-      const int sy = ly[u] + dy, sx = lx[u] + dx;
-      const bool inb = lok[u] && sy >= 0 && sy < H && sx >= 0 && sx < W;
-      const int64_t pix = ((int64_t)limg[u] * H + sy) * W + sx;
-      ra[u] = load8(x1, x2, none, pix, inb, c0 + lcol);
-      if (masked) rm[u] = load8(mask, none, none, pix, inb, c0 + lcol);
-    }
-    rb = make_uint4(0, 0, 0, 0);
-    const int co = n0 + lrow, ci = c0 + lcol;
-    if (bload && co < cout && ci < cin)
-      rb = *reinterpret_cast<const uint4*>(wk + ((int64_t)tap * cout + co) * cin + ci);
-  };
-  f32x4 acc[IM][2];
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  constexpr int WN = BNT / 32;   // wavefronts across the channels
-  const int wm = (wv % (4 / WN)) * 16 * IM, wn = (wv / (4 / WN)) * 32;
-  fetch(0);
-  for (int step = 0; step < nsteps; ++step) {
-    __syncthreads();   // the previous step's fragments have been read
-#pragma unroll
-    for (int u = 0; u < AR; ++u)
-      *reinterpret_cast<uint4*>(&sA[(lrow + 64 * u) * LDK + lcol]) =
-          masked ? apply_mask8(ra[u], rm[u]) : ra[u];
-    if (bload) *reinterpret_cast<uint4*>(&sB[lrow * LDK + lcol]) = rb;
-    __syncthreads();
-    if (step + 1 < nsteps) fetch(step + 1);
-    bf16x8 a[IM], b[2];
-#pragma unroll
-    for (int i = 0; i < IM; ++i)
-      a[i] = *reinterpret_cast<const bf16x8*>(&sA[(wm + i * 16 + (lane & 15)) * LDK + 8 * (lane >> 4)]);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      b[j] = *reinterpret_cast<const bf16x8*>(&sB[(wn + j * 16 + (lane & 15)) * LDK + 8 * (lane >> 4)]);
-#pragma unroll
-    for (int i = 0; i < IM; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-  }
-  // epilogue: bias, ReLU, bf16 (or float32) store
-#pragma unroll
-  for (int i = 0; i < IM; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int co = n0 + wn + j * 16 + (lane & 15);
-      if (co >= cout) continue;
-      const float bco = bias ? bias[co] : 0.f;
-      for (int r = 0; r < 4; ++r) {
-        const int64_t p = m0 + wm + i * 16 + 4 * (lane >> 4) + r;
-        if (p >= npix) continue;
-        float v = acc[i][j][r] + bco;
-        if (relu) v = fmaxf(v, 0.f);
-        if (y) y[p * y_stride + y_offset + co] = f2bf(v);
-        if (yf) yf[p * yf_stride + co] = v;
-      }
-    }
 }
 
 // Direct 3x3 convolution on spatial tiles.  A workgroup computes 16 x 16
@@ -432,6 +313,7 @@ __global__ __launch_bounds__(64 * PT / PR, 4) void conv3x3_patch_kernel(
 // inputs (input-channel tile) with 16-byte loads, and writes them transposed
 // ([channel][pixel], two pixels per 32-bit write) into LDS; each wavefront
 // then issues two K steps of four MFMAs per tap.
+constexpr int BM = 64, BN = 64;      // channels of a tile
 constexpr int WBK = 64;              // pixels per stage
 constexpr int WLDK = WBK + 8;        // LDS row pitch in bf16 (16-byte aligned rows)
 constexpr int kWgradBlocks = 512;    // pixel chunks are sized for about this many workgroups
@@ -1491,57 +1373,28 @@ hipError_t nn_conv3x3(const gs_act* x1, const gs_act* x2, const gs_act* mask, co
                       int cout, const float* bias, int relu, gs_act* y, float* yf, int yf_stride,
                       hipStream_t s) {
   const int cin = x1->c + (x2 ? x2->c : 0);
-  const int64_t npix = (int64_t)x1->n * x1->h * x1->w;
-  // Tiles: up to 32 output channels, 32-channel tiles (a 64-channel tile
-  // would spend half its MFMAs on channels that do not exist); 64 x 32
-  // wavefront blocks while that still gives about 1,024 workgroups, else
-  // 32 x 32 ones (twice the workgroups for the small deep layers).
   auto* yp = y ? static_cast<uint16_t*>(y->data) : nullptr;
   const int ys = y ? y->stride : 0, yo = y ? y->offset : 0;
   const auto* wp = static_cast<const uint16_t*>(w);
-  if (cin % 8 == 0 && x1->c % 8 == 0) {
-    const unsigned tiles = (unsigned)(x1->n * ((x1->h + PT - 1) / PT) * ((x1->w + PT - 1) / PT));
-    // 32 output channels per workgroup up to 32 channels, for an odd number of
-    // 32-channel groups (96 in 64-channel workgroups would waste a quarter of the
-    // products), and where 64-channel workgroups would number fewer than 1,024, two for
-    // each of the 512 places: half as much to a workgroup fills the places of a small
-    // layer and leaves less in the last turn of a middling one, while in a large one
-    // both halves of the channels would read the input.  The line at 512, 1,024 or
-    // 2,048 (us): 320x240, 128 -> 128 31, 28, 28; 8 x 160x120, 64 -> 64 21, 18, 18 and
-    // 384 -> 128 133, 130, 155.
-    const bool narrow =
-        cout <= 32 || cout % 64 == 32 || tiles * (unsigned)((cout + 63) / 64) < 1024u;
-    const bool one = cin <= PCC;
+  const unsigned tiles = (unsigned)(x1->n * ((x1->h + PT - 1) / PT) * ((x1->w + PT - 1) / PT));
+  // 32 output channels per workgroup up to 32 channels, for an odd number of
+  // 32-channel groups (96 in 64-channel workgroups would waste a quarter of the
+  // products), and where 64-channel workgroups would number fewer than 1,024, two for
+  // each of the 512 places: half as much to a workgroup fills the places of a small
+  // layer and leaves less in the last turn of a middling one, while in a large one
+  // both halves of the channels would read the input.  The line at 512, 1,024 or
+  // 2,048 (us): 320x240, 128 -> 128 31, 28, 28; 8 x 160x120, 64 -> 64 21, 18, 18 and
+  // 384 -> 128 133, 130, 155.
+  const bool narrow =
+      cout <= 32 || cout % 64 == 32 || tiles * (unsigned)((cout + 63) / 64) < 1024u;
+  const bool one = cin <= PCC;
 #define GS_PATCH(J, M, O)                                                                     \
   launch_patch<J, M, O>(view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias, \
                         relu, yp, ys, yo, yf, yf_stride, tiles, s)
-    if (narrow && one) return mask ? GS_PATCH(2, true, true) : GS_PATCH(2, false, true);
-    if (narrow) return mask ? GS_PATCH(2, true, false) : GS_PATCH(2, false, false);
-    return mask ? GS_PATCH(4, true, false) : GS_PATCH(4, false, false);
+  if (narrow && one) return mask ? GS_PATCH(2, true, true) : GS_PATCH(2, false, true);
+  if (narrow) return mask ? GS_PATCH(2, true, false) : GS_PATCH(2, false, false);
+  return mask ? GS_PATCH(4, true, false) : GS_PATCH(4, false, false);
 #undef GS_PATCH
-  }
-  const unsigned ntile = (unsigned)((cout + 63) / 64);
-  // (the masked backward-data calls measured faster without the large tiles)
-  const bool narrow = cout <= 32;
-  const bool big = mask == nullptr &&
-                   (int64_t)blocks(npix, narrow ? 256 : 128) * (narrow ? 1 : ntile) >= 1024;
-  if (narrow && big)
-    hipLaunchKernelGGL((conv3x3_kernel<256, 32, 4>), dim3(blocks(npix, 256), 1), dim3(256), 0, s,
-                       view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias,
-                       relu, yp, ys, yo, yf, yf_stride);
-  else if (narrow)
-    hipLaunchKernelGGL((conv3x3_kernel<128, 32, 2>), dim3(blocks(npix, 128), 1), dim3(256), 0, s,
-                       view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias,
-                       relu, yp, ys, yo, yf, yf_stride);
-  else if (big)
-    hipLaunchKernelGGL((conv3x3_kernel<128, 64, 4>), dim3(blocks(npix, 128), ntile), dim3(256), 0,
-                       s, view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias,
-                       relu, yp, ys, yo, yf, yf_stride);
-  else
-    hipLaunchKernelGGL((conv3x3_kernel<64, 64, 2>), dim3(blocks(npix, 64), ntile), dim3(256), 0,
-                       s, view(x1), view(x2), view(mask), x1->n, x1->h, x1->w, wp, cout, cin, bias,
-                       relu, yp, ys, yo, yf, yf_stride);
-  return hipGetLastError();
 }
 
 hipError_t nn_conv3x3_wgrad(const gs_act* x1, const gs_act* x2, const gs_act* dz,

@@ -88,8 +88,9 @@ typedef struct gs_camera {
 /* Gaussian map, structure of arrays, component-major float32 (device):
  *   means [3][n], log_scales [3][n], quats [4][n] in (w, x, y, z) order (not
  *   necessarily normalised), opacity_logits [n], sh [3][K][n] with
- *   K = (sh_degree + 1)^2.  Non-finite parameters or a zero quaternion cull
- *   the Gaussian. */
+ *   K = (sh_degree + 1)^2.  A non-finite mean, log scale, quaternion or
+ *   opacity logit or a zero quaternion culls the Gaussian; SH coefficients are
+ *   not looked at, so that a colour may be infinite. */
 typedef struct gs_gaussians {
   const float* means;
   const float* log_scales;
@@ -244,8 +245,10 @@ enum {
  * a 16x16 tile is covered by 256 / value threads; a staging batch holds
  * (splats per thread) x 256 / (pixels per lane) splats.  value 0 restores
  * the default.  Applies to launches enqueued after the call; a captured graph
- * keeps the configuration it was captured with.  Results are identical for
- * every setting up to float32 summation order of the gradient atomics. */
+ * keeps the configuration it was captured with.  Forward results are identical
+ * for every setting, gradients up to float32 summation order of the atomics
+ * and, where nothing is set and gs_render_bwd chooses to walk the lists of few
+ * tiles in parts, the rounding of what a part starts from. */
 int gs_set_tuning(int key, int value);
 /* Current value of a tuning key (< 0 for an unknown key); 1 for pixels per
  * lane that the launch chooses. */
@@ -285,7 +288,9 @@ size_t gs_bin_sort_workspace_size(int64_t n, const gs_views* views, int64_t capa
  * equal keys keep ascending value order) and writes per-tile ranges.
  * n_keys_host != NULL: waits once, for the key count (not for the sort); if
  * it exceeds bins->capacity, *n_keys_host holds the required capacity, no key
- * is placed, the stream is synchronised and GS_ERR_CAPACITY is returned.
+ * is placed, the stream is synchronised and GS_ERR_CAPACITY is returned.  A
+ * call that returns GS_OK has not synchronised the stream: a caller that reads
+ * on the host what the stream's earlier work wrote synchronises itself.
  * n_keys_host == NULL: no synchronisation (capture-safe); keys beyond the
  * capacity are dropped and bins->n_keys reports the full count, which the
  * caller must check against the capacity after the stream completes. */

@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kBlock / PPL) void render_bwd_kernel(
 // three to four of them share a SIMD without slowing each other, but 300 tiles leave it
 // with one, and two on the 44 CUs that hold two tiles.  (Four wavefronts per quadrant of
 // whole tiles, 1,024 threads, gained nothing: those CUs had the work of two.)
-// Kernel alone: 300 tiles of the tracking step 66 -> 44 us, 320 of a local one 39 -> 31.
+// Kernel alone: 300 tiles of the tracking step 66 -> 45 us, 320 of a local one 39 -> 31.
 // Whole backward, one wavefront | four (us): 12 tiles 60 | 32, 300 of 100,000 Gaussians
 // 123 | 72, 768 97 | 71, 945 88 | 77, 1,200 72 | 86 and, with long lists, 111 | 102.
 constexpr int kSplit = 4;          // quarters of a list: wavefronts

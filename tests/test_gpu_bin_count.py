@@ -146,7 +146,10 @@ def test_refused_wait_leaves_nothing_under_way(gs):
     call = _setup(gs, 300, 6, 1 << 16)
     want = gs.gs_bin_sort(*call, sync=True)
     a = torch.randn(8192, 8192, device="cuda")
-    recorded, stream = torch.cuda.Stream(), torch.cuda.Stream()
+    stream = torch.cuda.Stream()
+    # a stream of its own: a spoilt recording leaves it unfit for the next one
+    recorded, graph = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipStreamCreateWithFlags(ctypes.byref(recorded), 1) == 0   # non-blocking
     torch.cuda.synchronize()
     with torch.cuda.stream(stream):
         for _ in range(10):   # a tenth of a second in front of the call's kernels
@@ -162,12 +165,12 @@ def test_refused_wait_leaves_nothing_under_way(gs):
         hip.hipThreadExchangeStreamCaptureMode(ctypes.byref(mode))
         seen.append(stream.query())
 
-    handle, graph = ctypes.c_void_p(recorded.cuda_stream), ctypes.c_void_p()
-    assert hip.hipStreamBeginCapture(handle, 0) == 0   # global
+    assert hip.hipStreamBeginCapture(recorded, 0) == 0   # global
     t = threading.Thread(target=work)
     t.start()
     t.join()
-    hip.hipStreamEndCapture(handle, ctypes.byref(graph))   # the refused wait has spoilt it
+    hip.hipStreamEndCapture(recorded, ctypes.byref(graph))   # the refused wait has spoilt it
+    hip.hipStreamDestroy(recorded)
     hip.hipGetLastError()
     assert seen == [gs.GS_ERR_HIP, True]
     assert gs.gs_bin_sort(*call, sync=True) == want
